@@ -50,10 +50,12 @@ KERNEL_FLAGS = ["-mno-amdgpu-ieee", "-fno-honor-nans",
                 "-mllvm", "-pragma-unroll-threshold=100000"]
 
 
-# The kernel source is compiled twice (FABFT_PART 0 and 1, see its head): the
-# second part, the d = 128 forward kernels without the weighted check, with
-# LLVM's iterative ILP scheduler.
+# The kernel source is compiled three times (FABFT_PART 0 to 2, see its head):
+# part 1, the d = 128 forward kernels without the weighted check, with LLVM's
+# iterative ILP scheduler; part 2, the d = 256 forward kernels, with MFMA
+# results in vector registers first.
 PART1_FLAGS = ["-DFABFT_PART=1", "-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]
+PART2_FLAGS = ["-DFABFT_PART=2", "-mllvm", "-amdgpu-mfma-vgpr-form=1"]
 
 
 def build_cmds(out: str, objdir: str, extra=()) -> list[list[str]]:
@@ -61,13 +63,16 @@ def build_cmds(out: str, objdir: str, extra=()) -> list[list[str]]:
     hipcc = hipcc_path()
     k_obj = os.path.join(objdir, "fabft_kernels.o")
     k1_obj = os.path.join(objdir, "fabft_kernels_part1.o")
+    k2_obj = os.path.join(objdir, "fabft_kernels_part2.o")
     a_obj = os.path.join(objdir, "fabft_api.o")
     return [
         [hipcc, "-x", "hip", *COMMON, *KERNEL_FLAGS, *inc, *extra, "-c", SOURCES[0], "-o", k_obj],
         [hipcc, "-x", "hip", *COMMON, *KERNEL_FLAGS, *PART1_FLAGS, *inc, *extra, "-c", SOURCES[0],
          "-o", k1_obj],
+        [hipcc, "-x", "hip", *COMMON, *KERNEL_FLAGS, *PART2_FLAGS, *inc, *extra, "-c", SOURCES[0],
+         "-o", k2_obj],
         [hipcc, "-x", "hip", *COMMON, *inc, *extra, "-c", SOURCES[1], "-o", a_obj],
-        [hipcc, f"--offload-arch={ARCH}", "-shared", "-fPIC", k_obj, k1_obj, a_obj, "-o", out],
+        [hipcc, f"--offload-arch={ARCH}", "-shared", "-fPIC", k_obj, k1_obj, k2_obj, a_obj, "-o", out],
     ]
 
 

@@ -76,11 +76,15 @@
 
 #include "fabft_kernels.h"
 
-// This file is compiled twice. Part 0 holds everything except the d = 128
-// forward kernels without the weighted check; part 1 holds only those and
-// is built with LLVM's iterative ILP scheduler, measured 2-3% faster for
-// them (and 2-4% slower at d = 64, which therefore stays in part 0). A
-// kernel is instantiated in one part only.
+// This file is compiled three times. Part 1 holds the d = 128 forward kernels
+// without the weighted check and is built with LLVM's iterative ILP scheduler,
+// measured 2-3% faster for them (and 2-4% slower at d = 64). Part 2 holds the
+// d = 256 forward kernels and is built with the MFMA results in vector
+// registers first (-amdgpu-mfma-vgpr-form): by default LLVM puts every MFMA
+// result into the accumulation registers of these 512-register kernels and
+// copies the scores out and the outputs back and forth, about 400 copies per
+// key tile and wave, against about 50. Part 0 holds everything else. A kernel
+// is instantiated in one part only.
 #ifndef FABFT_PART
 #define FABFT_PART 0
 #endif
@@ -97,6 +101,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 
 // Workgroup shape per row width D: WAVES waves of 32 query rows, an LDS ring
 // of STAGES key tiles, AHEAD of them loading while one is in use. D = 256
@@ -195,11 +200,11 @@ __device__ __forceinline__ int swap_bits23(int r) {
   return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1);
 }
 
-// s_waitcnt vmcnt(n) (expcnt and lgkmcnt left unconstrained), n < 16
+// s_waitcnt vmcnt(n) (expcnt and lgkmcnt left unconstrained), n < 64
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 16, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt(N | (0x7 << 4) | (0xF << 8));
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
 // buffer_load_dwordx4 ... lds through a buffer resource (base, size in
@@ -240,10 +245,12 @@ __device__ __forceinline__ void buffer_load_lds16(i32x4 rsrc, uint32_t voff, uin
 template <int D>
 struct Tile {
   static constexpr int CPR = D / 8;
+  // (at d >= 128 a row spans all 64 banks or twice that, at d = 64 half of
+  // them)
   // K: 16 lanes read 16 different rows at one logical chunk
-  static __device__ __forceinline__ int kswz(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
+  static __device__ __forceinline__ int kswz(int r) { return D >= 128 ? (r & 15) : ((r >> 1) & 7); }
   // V: 32 lanes read 4 consecutive rows x 4 consecutive chunks
-  static __device__ __forceinline__ int vswz(int r) { return D == 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1); }
+  static __device__ __forceinline__ int vswz(int r) { return D >= 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1); }
   static __device__ __forceinline__ int kidx(int r, int c) { return r * D + 8 * (c ^ kswz(r)); }
   static __device__ __forceinline__ int vidx(int r, int c) { return r * D + 8 * (c ^ vswz(r)); }
 };
@@ -1229,6 +1236,516 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
   }
 }
 
+#if FABFT_PART == 2
+// ---- d = 256: the forward (checksum on, off or weighted) with the next
+// tile's scores taken beside this tile's softmax. Row by row the operations
+// and their order are fwd_kernel's, so O, resid and flags are bitwise the same.
+//
+// At d = 256 one wave runs per SIMD (Q and o fill its registers), so no second
+// wave covers its waits: in fwd_kernel's order (Q K^T, max, exponentials, P V)
+// the matrix cores stood idle during the softmax and were busy 29% of the time.
+// Here step t issues Q K^T of tile t + 1 with the exponentials of tile t and
+// the tile's row sums (sumrow) between the products, then P V of tile t with
+// the max of tile t + 1 between them (two score buffers). Causal
+// prefill, B=1 H=16 L=4096: 187 -> 158 us with the checksum, 160 -> 146 us
+// without (MFMA busy 29 -> 36%); what is left is the LDS: without the tile
+// loads the step takes 11% less, without K's operand reads 11% less. The
+// same pipeline at d = 128 and 64 (two waves per SIMD, 32 rows each) measured
+// 3-4% slower than fwd_kernel: there the vector ALU, which the products beside
+// it do not relieve, and the LDS set the pace; one wave per SIMD with 64 rows
+// at d = 128 measured 15-25% slower (issue of one wave: 5 cycles per
+// instruction).
+template <bool CAUSAL, bool CHECK, bool WCHK>
+__global__ __launch_bounds__(Cfg<256>::THREADS, 1) void wide_kernel(FwdParams p) {
+  constexpr int D = 256, BC = kBc, kThreads = Cfg<D>::THREADS, kBr = Cfg<D>::BR;
+  constexpr int CPR = Tile<D>::CPR;
+  constexpr int NKB = BC / 32;    // 32-key blocks per tile
+  constexpr int NDB = D / 32;     // 32-column blocks of the output
+  constexpr int NDS = D / 16;     // 16-wide steps over d in Q K^T
+  constexpr int NLD = BC * CPR / kThreads;   // 16-byte loads per thread per tensor and tile
+  static_assert(Cfg<D>::STAGES == 2 && Cfg<D>::WAVES == 4, "one wave per SIMD, two stages");
+
+  __shared__ __attribute__((aligned(16))) Ring<D> ring;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
+  const int mrow = lane & 31;   // MFMA row / column index of this lane
+  const int grp = lane >> 5;    // which 8-wide k slice this lane holds
+
+  int bh = 0, qt = 0;
+  item_of_block<CAUSAL>(p, blockIdx.x, bh, qt);
+  bh = __builtin_amdgcn_readfirstlane(bh);
+  qt = __builtin_amdgcn_readfirstlane(qt);
+
+  const int Lq = p.Lq, Lk = p.Lk;
+  const int off = Lk - Lq;
+  const uint32_t kv_bytes = (uint32_t)Lk * D * 2;
+  const float sl2 = p.sl2;
+  // key tiles of the workgroup [0, t_end) and of this wave [0, my_end): a wave
+  // skips the tiles past its last row's diagonal, and all of them when it
+  // holds no row below Lq
+  int kend = Lk;
+  if (CAUSAL) kend = min(Lk, qt * kBr + kBr + off);
+  const int t_end = __builtin_amdgcn_readfirstlane(kend > 0 ? (kend + BC - 1) / BC : 0);
+  const int wq_lo = __builtin_amdgcn_readfirstlane(qt * kBr + 32 * wave);
+  const int qrow = wq_lo + mrow;
+  int my_end = t_end;
+  if (CAUSAL) my_end = min(t_end, wq_lo + 31 + off < 0 ? 0 : (wq_lo + 31 + off) / BC + 1);
+  if (wq_lo >= Lq) my_end = 0;
+  my_end = __builtin_amdgcn_readfirstlane(my_end);
+
+  // ---- Q fragments (B operand): lane holds query qrow, d slice 8*grp
+  u32x4 qf[NDS];
+  {
+    const uint16_t* qr = p.q + ((size_t)bh * (size_t)Lq + (size_t)qrow) * D;
+#pragma unroll
+    for (int s = 0; s < NDS; ++s) {
+      qf[s] = u32x4{0, 0, 0, 0};
+      if (qrow < Lq) qf[s] = *reinterpret_cast<const u32x4*>(qr + 16 * s + 8 * grp);
+    }
+  }
+
+  f32x16 oacc[NDB], sa[NKB], sb[NKB];   // output; scores of the current and the next tile
+  f32x4 aux = {}, auxw = {};
+  float m2_run = -__builtin_inff(), nm2 = 0.f, alpha = 1.f;
+#pragma unroll
+  for (int db = 0; db < NDB; ++db) oacc[db] = f32x16{};
+
+  // constant rows of the c / l operand (visible after the first barrier)
+  for (int e = tid; e < 2 * 2 * BC; e += kThreads) {
+    const int st_i = e / (2 * BC), row = kRowOnes + (e / BC) % 2, key = e % BC;
+    ring.vsm[st_i][row][key] = row == kRowOnes ? (uint16_t)0x3f80 : (uint16_t)0;
+  }
+  const int vsm_row4 = (lane & 3) == 2 ? (int)kRowOnes
+                       : (!CHECK || (lane & 3) == 3) ? (int)kRowZero
+                                                     : (lane & 3);
+  const int vsm_roww = (lane & 3) < 2 ? (int)kRowWHi + (lane & 3) : (int)kRowZero;
+
+  // ---- loader: as in fwd_kernel; the rows of a thread's loads are kRowStep
+  // apart, two loads span a period of the swizzles (16 rows), so two per-lane
+  // offsets per tensor serve them all
+  constexpr int kRowStep = kThreads / CPR, NOFF = 16 / kRowStep;
+  static_assert(kRowStep * CPR == kThreads && NOFF * kRowStep == 16 && NLD % NOFF == 0, "swizzle period");
+  uint32_t kvo[NOFF], vvo[NOFF];
+#pragma unroll
+  for (int j = 0; j < NOFF; ++j) {
+    const int row = j * kRowStep + tid / CPR, sc = tid % CPR;
+    kvo[j] = (uint32_t)(row * D + 8 * (sc ^ Tile<D>::kswz(row))) * 2;
+    vvo[j] = (uint32_t)(row * D + 8 * (sc ^ Tile<D>::vswz(row))) * 2;
+  }
+  const uint32_t ring_lds = (uint32_t)(uintptr_t)(lds_void*)&ring;
+  const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(ring_lds + 1024u * wave);
+  const size_t kvbase = (size_t)bh * (size_t)Lk * D;
+  const i32x4 krs = buffer_rsrc(p.k + kvbase, kv_bytes), vrs = buffer_rsrc(p.v + kvbase, kv_bytes);
+  constexpr uint32_t kStage = sizeof(Ring<D>::k[0]), kTile = BC * D * 2;
+  static_assert(kStage == kTile, "a stage holds one tile");
+  // load pair j of a tile of K (V) at byte soff of the head into stage S: two
+  // loads behind one wait for the resource's registers (buffer_load_lds16).
+  // Tiles past the item's last one are loaded too (zeros past the head's end),
+  // so that every step issues the same number of loads; nothing reads them
+  static_assert(NOFF == 2, "the loads of a pair");
+  auto load_op = [&](int S, bool isv, uint32_t soff, int j) __attribute__((always_inline)) {
+    uint32_t m0 = __builtin_amdgcn_readfirstlane(
+        wave_lds + (isv ? (uint32_t)offsetof(Ring<D>, v) : (uint32_t)offsetof(Ring<D>, k)) +
+        S * kStage + 2 * j * kThreads * 16);
+    const uint32_t so = __builtin_amdgcn_readfirstlane(soff + (uint32_t)(j * 16 * D * 2));
+    asm volatile(
+        "s_nop 4\n\tbuffer_load_dwordx4 %1, %3, %4 offen lds\n\t"
+        "s_add_u32 m0, m0, %5\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds"
+        : "+{m0}"(m0)
+        : "v"(isv ? vvo[0] : kvo[0]), "v"(isv ? vvo[1] : kvo[1]), "s"(isv ? vrs : krs), "s"(so),
+          "i"(kThreads * 16)
+        : "memory", "scc");
+  };
+  constexpr int NLP = NLD / 2;
+  auto issue = [&](int S, bool isv, int t) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < NLP; ++j) load_op(S, isv, (uint32_t)t * kTile, j);
+  };
+
+  // the value, opaque to the optimiser (one instruction per derived address
+  // instead of a re-association with its parts)
+  auto opaque = [](uint32_t x) __attribute__((always_inline)) {
+    asm volatile("" : "+v"(x));
+    return x;
+  };
+  // ---- sumrow(V) of the tile in stage S (Eq. 4), four threads per key, as in
+  // fwd_kernel, in kSumOps micro steps
+  constexpr int TPK = kThreads / BC, CPT = CPR / TPK, kSumOps = 2 * CPT + 2;
+  struct SumState {
+    u32x4 ch[CPT];
+    float a, aw;
+    uint32_t base;
+  };
+  const int skey = tid / TPK, spart = tid % TPK;
+  auto sum_op = [&](int S, SumState& st, int n) __attribute__((always_inline)) {
+    if (n < CPT) {
+      // chunks CPT * spart + n; the swizzle of a key is a constant XOR
+      if (n == 0) {
+        st.base = opaque(ring_lds + (uint32_t)offsetof(Ring<D>, v) + S * kStage + 2 * Tile<D>::vidx(skey, CPT * spart));
+        st.a = st.aw = 0.f;
+      }
+      st.ch[n] = *reinterpret_cast<const lds_u32x4*>((uintptr_t)(st.base ^ (16u * n)));
+    } else if (n < 2 * CPT) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        st.a = dot2(st.ch[n - CPT][e], kOnes, st.a);
+        if constexpr (WCHK) st.aw = dot2(st.ch[n - CPT][e], kAlt, st.aw);
+      }
+    } else if (n == 2 * CPT) {
+      st.a = group_sum<TPK>(st.a);
+      if constexpr (WCHK) st.aw = group_sum<TPK>(st.aw);
+    } else {
+      // all four threads of a key hold the sums and write the same values (no
+      // branch inside the interleaved step)
+      const uint32_t hi = pack_bf16x2(st.a, 0.f) & 0xffffu;
+      const uint32_t lo = pack_bf16x2(st.a - __uint_as_float(hi << 16), 0.f) & 0xffffu;
+      ring.vsm[S][kRowVsHi][skey] = (uint16_t)hi;
+      ring.vsm[S][kRowVsLo][skey] = (uint16_t)lo;
+      if constexpr (WCHK) {
+        const uint32_t whi = pack_bf16x2(st.aw, 0.f) & 0xffffu;
+        const uint32_t wlo = pack_bf16x2(st.aw - __uint_as_float(whi << 16), 0.f) & 0xffffu;
+        ring.vsm[S][kRowWHi][skey] = (uint16_t)whi;
+        ring.vsm[S][kRowWLo][skey] = (uint16_t)wlo;
+      }
+    }
+  };
+  auto sumrow = [&](int S) __attribute__((always_inline)) {
+    SumState st;
+#pragma unroll
+    for (int n = 0; n < kSumOps; ++n) sum_op(S, st, n);
+  };
+
+  // ---- operand reads. The swizzles only touch address bits that the step
+  // over d (K) or the column block (V) set, so a read is a per-lane base with
+  // those bits XORed in, plus an immediate offset.
+  const int krow = swap_bits23(mrow);
+  constexpr int NQK = NDS * NKB, NPV = NKB * 2 * NDB;
+  constexpr uint32_t kRow = 2 * D;   // bytes per tile row
+  const uint32_t klane = ring_lds + (uint32_t)offsetof(Ring<D>, k) + 2 * Tile<D>::kidx(krow, grp);
+  const int gq = lane >> 4, ll = lane & 15;
+  const uint32_t vlane = ring_lds + (uint32_t)offsetof(Ring<D>, v) +
+                         2 * (Tile<D>::vidx(8 * (gq >> 1) + (ll >> 2), 2 * (gq & 1) + ((ll >> 1) & 1)) +
+                              4 * (ll & 1));
+  // Q K^T operand i: key block i / NDS, step i % NDS over d; kt is klane in
+  // the tile's stage
+  auto kread = [&](uint32_t kt, int i) __attribute__((always_inline)) {
+    const uint32_t a = (kt ^ (32u * (i % NDS))) + (i / NDS) * 32 * kRow;
+    return *reinterpret_cast<const lds_u32x4*>((uintptr_t)a);
+  };
+  // P V operand i = (key block, 16-key step, column block); vt is vlane in the
+  // tile's stage
+  auto vread = [&](uint32_t vt, int i) __attribute__((always_inline)) {
+    const int kb = i / (2 * NDB), h = (i / NDB) % 2, db = i % NDB;
+    u32x2 part[2];
+#pragma unroll
+    for (int t2 = 0; t2 < 2; ++t2) {
+      const uint32_t a = (vt ^ (64u * db)) + (32 * kb + 16 * h + 4 * t2) * kRow;
+      part[t2] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)a));
+    }
+    return u32x4{part[0][0], part[0][1], part[1][0], part[1][1]};
+  };
+
+  // ---- pieces of a tile's softmax, the operations of fwd_kernel in its order
+  constexpr int NPR = 8 * NKB;   // pairs of scores per lane and tile
+  auto epair = [&](f32x16 (&s)[NKB], u32x4 (&pb)[NKB][2], int n) __attribute__((always_inline)) {
+    const int kb = n / 8, j = n % 8;
+    const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][2 * j], sl2, nm2));
+    const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][2 * j + 1], sl2, nm2));
+    // (the empty asm keeps the compiler from sinking the exponentials past the
+    // branches below)
+    uint32_t pk = pack_bf16x2(p0, p1);
+    asm volatile("" : "+v"(pk));
+    pb[kb][j >> 2][j & 3] = pk;
+  };
+  // a masked score is -inf; bit e of vis: score e (of the lane's key
+  // 16 (e / 8) + e % 8) is visible
+  auto mask_tile = [&](f32x16 (&s)[NKB], int kv0) __attribute__((always_inline)) {
+    int lim = Lk - 1;
+    if (CAUSAL) lim = min(lim, qrow + off);
+    const int rel = lim - (kv0 + 8 * grp);
+    uint32_t vis = 0;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) vis |= ((1u << min(max(rel + 1 - 16 * g, 0), 8)) - 1u) << (8 * g);
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)vis, 16 * kb + i, 1);
+        s[kb][i] = __uint_as_float((__float_as_uint(s[kb][i]) & m) | (0xff800000u & ~m));
+      }
+  };
+  auto need_mask = [&](int t) {
+    const int kv0 = t * BC;
+    return (kv0 + BC > Lk) || (CAUSAL && kv0 + BC - 1 > wq_lo + off);
+  };
+  float mx = 0.f, m_new = 0.f;
+  auto max_op = [&](f32x16 (&s)[NKB], int n) __attribute__((always_inline)) {
+    const int kb = n / 8, j = n % 8;
+    if (n == 0) mx = __builtin_fmaxf(s[0][0], s[0][1]);
+    else mx = __builtin_fmaxf(__builtin_fmaxf(mx, s[kb][2 * j]), s[kb][2 * j + 1]);
+  };
+  // lazy running max of the tile just scored, in kFinOps micro steps
+  constexpr int kFinOps = 4;
+  auto fin_op = [&](int n) __attribute__((always_inline)) {
+    if (n == 0) {
+      mx = max_xor32(mx);
+    } else if (n == 1) {
+      mx = (mx == -__builtin_inff()) ? -__builtin_inff() : mx * sl2;
+    } else if (n == 2) {
+      m_new = (mx > m2_run + kLazy) ? mx : m2_run;
+    } else {
+      alpha = (m_new == m2_run) ? 1.f : __builtin_amdgcn_exp2f(m2_run - m_new);
+      m2_run = m_new;
+      nm2 = (m_new == -__builtin_inff()) ? 0.f : -m_new;
+    }
+  };
+  auto rescale = [&]() __attribute__((always_inline)) {
+    if (__ballot(alpha != 1.f)) {
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[db][i] *= alpha;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) aux[i] *= alpha;
+      if constexpr (WCHK) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) auxw[i] *= alpha;
+      }
+    }
+  };
+  // c / l products of the first (n = 0) or second 8 keys per lane of the
+  // 16-key step (kb, h)
+  u32x4 ax, axw;
+  auto aux_op = [&](int S, u32x4 (&pb)[NKB][2], int kb, int h, int n) __attribute__((always_inline)) {
+    if (n == 0) ax = *reinterpret_cast<const u32x4*>(&ring.vsm[S][vsm_row4][32 * kb + 16 * h + 8 * grp]);
+    aux = mfma4(u32x2{ax[2 * n], ax[2 * n + 1]}, u32x2{pb[kb][h][2 * n], pb[kb][h][2 * n + 1]}, aux);
+    if constexpr (WCHK) {
+      if (n == 0) axw = *reinterpret_cast<const u32x4*>(&ring.vsm[S][vsm_roww][32 * kb + 16 * h + 8 * grp]);
+      auxw = mfma4(u32x2{axw[2 * n], axw[2 * n + 1]}, u32x2{pb[kb][h][2 * n], pb[kb][h][2 * n + 1]}, auxw);
+    }
+  };
+  // keep Q in the accumulation registers, which leaves the vector registers to
+  // the scores
+  auto pin_q = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < NDS; ++s) asm volatile("" : "+a"(qf[s]));
+  };
+
+  // A branch that is never taken, to end the basic block: with the loop's
+  // head, the row sums and the products in one block the register allocator
+  // spills (no instantiation does with the split).
+  auto split_block = [&]() __attribute__((always_inline)) {
+    if (Lq < 0) asm volatile("s_nop 0");
+  };
+  // ---- tile t (in cur, its max taken) with the scores of tile t + 1 (into
+  // nx): the exponentials run between the Q K^T products, the next tile's max
+  // between the P V products. Operands are read in groups of GK (GV), one
+  // group ahead, so that one wait serves a group.
+  constexpr int GK = 2, GV = 2;
+  constexpr int E1 = 10;   // pairs of exponentials beside Q K^T, the rest beside P V's first half
+  static_assert(E1 >= NPR / 2 && E1 <= NPR, "the first key block is ready for P V");
+  constexpr int NSUM = CHECK ? kSumOps : 0;
+  auto full = [&](f32x16 (&cur)[NKB], f32x16 (&nx)[NKB], int t) __attribute__((always_inline)) {
+    const int S = t & 1, SN = S ^ 1;
+    const uint32_t kt = opaque(klane + SN * kStage), vt = opaque(vlane + S * kStage);
+    u32x4 pb[NKB][2], kop[NQK], vop[NPV];
+    split_block();
+    SumState st;
+    pin_q();
+#pragma unroll
+    for (int i = 0; i < GK; ++i) kop[i] = kread(kt, i);
+#pragma unroll
+    for (int i = 0; i < NQK; ++i) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (i % GK == 0) {
+#pragma unroll
+        for (int j = i + GK; j < i + 2 * GK && j < NQK; ++j) kop[j] = kread(kt, j);
+      }
+      if (i == NQK - GK) {
+#pragma unroll
+        for (int j = 0; j < GV; ++j) vop[j] = vread(vt, j);
+      }
+      nx[i / NDS] = mfma32(kop[i], qf[i % NDS], i % NDS == 0 ? f32x16{} : nx[i / NDS]);
+#pragma unroll
+      for (int n = i * NLP / NQK; n < (i + 1) * NLP / NQK; ++n) load_op(SN, true, (uint32_t)(t + 1) * kTile, n);
+#pragma unroll
+      for (int n = i * NSUM / NQK; n < (i + 1) * NSUM / NQK; ++n) sum_op(S, st, n);
+#pragma unroll
+      for (int n = i * E1 / NQK; n < (i + 1) * E1 / NQK; ++n) epair(cur, pb, n);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (need_mask(t + 1)) mask_tile(nx, (t + 1) * BC);
+    pin_q();
+    rescale();
+    pin_q();
+    split_block();
+    if constexpr (CHECK) __syncthreads();   // the tile's row sums are in
+    constexpr int H2 = NPV / 2, ER = NPR - E1, MS = H2 * 5 / 8, FS = H2 - MS;
+#pragma unroll
+    for (int i = 0; i < NPV; ++i) {
+      const int kb = i / (2 * NDB), h = (i / NDB) % 2, db = i % NDB;
+      __builtin_amdgcn_sched_barrier(0);
+      if (i % GV == 0) {
+#pragma unroll
+        for (int j = i + GV; j < i + 2 * GV && j < NPV; ++j) vop[j] = vread(vt, j);
+      }
+      oacc[db] = mfma32(vop[i], pb[kb][h], oacc[db]);
+#pragma unroll
+      for (int n = i * NLP / NPV; n < (i + 1) * NLP / NPV; ++n) load_op(S, false, (uint32_t)(t + 2) * kTile, n);
+      if (db == 0) aux_op(S, pb, kb, h, 0);
+      if (db == 3) aux_op(S, pb, kb, h, 1);
+      if (i < H2) {
+#pragma unroll
+        for (int n = E1 + i * ER / H2; n < E1 + (i + 1) * ER / H2; ++n) epair(cur, pb, n);
+      } else if (i - H2 < MS) {
+#pragma unroll
+        for (int n = (i - H2) * NPR / MS; n < (i - H2 + 1) * NPR / MS; ++n) max_op(nx, n);
+      } else {
+#pragma unroll
+        for (int n = (i - H2 - MS) * kFinOps / FS; n < (i - H2 - MS + 1) * kFinOps / FS; ++n) fin_op(n);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    pin_q();
+    split_block();
+  };
+  // the wave's last tile: no next scores to overlap
+  auto tail = [&](f32x16 (&cur)[NKB], int t) __attribute__((always_inline)) {
+    const int S = t & 1;
+    const uint32_t vt = opaque(vlane + S * kStage);
+    u32x4 pb[NKB][2];
+    issue(S ^ 1, true, t + 1);
+    issue(S, false, t + 2);
+    if constexpr (CHECK) sumrow(S);
+#pragma unroll
+    for (int n = 0; n < NPR; ++n) epair(cur, pb, n);
+    rescale();
+    if constexpr (CHECK) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NPV; ++i) {
+      const int kb = i / (2 * NDB), h = (i / NDB) % 2, db = i % NDB;
+      const u32x4 vo = vread(vt, i);
+      if (db == 0) aux_op(S, pb, kb, h, 0);
+      if (db == 3) aux_op(S, pb, kb, h, 1);
+      oacc[db] = mfma32(vo, pb[kb][h], oacc[db]);
+    }
+  };
+  // start of step t: K of tile t + 1 and V of tile t are in; every wave is
+  // done with K of tile t and V of tile t - 1, whose stages take K of tile
+  // t + 2 and V of tile t + 1 during the step
+  auto top = [&]() __attribute__((always_inline)) {
+    wait_vmcnt<0>();
+    __syncthreads();
+  };
+
+  if (t_end > 0) {
+    issue(0, false, 0);
+    issue(0, true, 0);
+    issue(1, false, 1);
+    wait_vmcnt<2 * NLD>();   // K of tile 0
+    __syncthreads();
+    // a use of Q here puts the compiler's own wait for its loads before the loop
+#pragma unroll
+    for (int s = 0; s < NDS; ++s) asm volatile("" : : "v"(qf[s]));
+    int t = 0;
+    if (my_end > 0) {
+      // first tile: scores, mask, max, with nothing to overlap
+#pragma unroll
+      for (int i = 0; i < NQK; ++i)
+        sa[i / NDS] = mfma32(kread(klane, i), qf[i % NDS], i % NDS == 0 ? f32x16{} : sa[i / NDS]);
+      if (need_mask(0)) mask_tile(sa, 0);
+#pragma unroll
+      for (int n = 0; n < NPR; ++n) max_op(sa, n);
+#pragma unroll
+      for (int n = 0; n < kFinOps; ++n) fin_op(n);
+      // the steps alternate between the two score buffers and end in sa: an
+      // even tile count starts in sb
+      bool half = !(my_end & 1);
+      if (half) {
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) sb[kb] = sa[kb];
+      }
+      while (t + 1 < my_end) {
+        if (!half) {
+          top();
+          full(sa, sb, t);
+          ++t;
+        }
+        half = false;
+        top();
+        full(sb, sa, t);
+        ++t;
+      }
+      top();
+      tail(sa, t);
+      ++t;
+    }
+    for (; t < t_end; ++t) {   // the other waves' tiles: loads and row sums
+      top();
+      issue((t & 1) ^ 1, true, t + 1);
+      issue(t & 1, false, t + 2);
+      if constexpr (CHECK) {
+        sumrow(t & 1);
+        __syncthreads();
+      }
+    }
+    wait_vmcnt<0>();   // no load may land in the LDS after the workgroup
+  }
+
+  // ---- epilogue: O = o / l (Alg. 3), pred = c / l (Eq. 8), check, as in
+  // fwd_kernel
+  const float l_tot = sum_xor32(aux[2]);
+  const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+  float act = 0.f, absum = 0.f, act_w = 0.f;
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float x = oacc[db][i] * inv;
+      oacc[db][i] = x;
+      act += x;
+      absum += __builtin_fabsf(x);
+      // column 32db + 8(i/4) + 4grp + i%4 is even iff i is even
+      act_w += (i & 1) ? -x : x;
+    }
+  if (qrow < Lq) {
+    uint16_t* orow = p.o + ((size_t)bh * (size_t)Lq + (size_t)qrow) * D;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        const u32x2 w = {pack_bf16x2(oacc[db][4 * a], oacc[db][4 * a + 1]),
+                         pack_bf16x2(oacc[db][4 * a + 2], oacc[db][4 * a + 3])};
+        *reinterpret_cast<u32x2*>(orow + 32 * db + 8 * a + 4 * grp) = w;
+      }
+  }
+  if constexpr (CHECK) {
+    act = sum_xor32(act);
+    absum = sum_xor32(absum);
+    const float pred = sum_xor32(aux[0] + aux[1]) * inv;
+    const float r = pred - act;
+    // non-finite residuals and overflowed sums, as in fwd_kernel
+    bool nonfinite = nonfinite_bits(r) || nonfinite_bits(absum);
+    uint8_t f = (__builtin_fabsf(r) <= p.tau_rel * (absum + __builtin_fabsf(pred)) + p.tau_abs) ? 0 : 1;
+    if constexpr (WCHK) {
+      act_w = sum_xor32(act_w);
+      const float pred_w = sum_xor32(auxw[0] + auxw[1]) * inv;
+      const float rw = pred_w - act_w;
+      nonfinite = nonfinite || nonfinite_bits(rw);
+      if (!(__builtin_fabsf(rw) <= p.tau_rel * (absum + __builtin_fabsf(pred_w)) + p.tau_abs)) f |= 4;
+    }
+    if (nonfinite) f |= 3;
+    if (grp == 0 && qrow < Lq) {
+      const size_t ri = (size_t)bh * Lq + qrow;
+      p.resid[ri] = r;
+      p.flags[ri] = f;
+    }
+  }
+}
+#endif  // FABFT_PART == 2
+
 // ---- persistent launches: how many workgroups the device holds at once
 #if FABFT_PART == 0
 std::atomic<int> g_persist{kPersistAuto};
@@ -1293,7 +1810,9 @@ static int launch_t(const FwdParams& p0, hipStream_t stream) {
 // instantiations, below
 template <int D, bool CAUSAL>
 static int launch_c(const FwdParams& p, int mode, hipStream_t s) {
-  if (mode == 0) return launch_t<D, CAUSAL, false, false, false, false>(p, s);
+  if constexpr (D != 256) {   // wide_kernel runs modes 0 and 1 at d = 256
+    if (mode == 0) return launch_t<D, CAUSAL, false, false, false, false>(p, s);
+  }
   if (mode == 4) return launch_t<D, CAUSAL, true, false, false, false, false, true>(p, s);
   if (mode == 5) return launch_t<D, CAUSAL, true, true, false, false, false, true>(p, s);
   if constexpr (D != 256) {
@@ -1302,8 +1821,8 @@ static int launch_c(const FwdParams& p, int mode, hipStream_t s) {
       if (mode == 1) return launch_t<D, CAUSAL, true, false, false, false, true>(p, s);
       return launch_t<D, CAUSAL, true, true, false, false, true>(p, s);
     }
+    if (mode == 1) return launch_t<D, CAUSAL, true, false, false, false>(p, s);
   }
-  if (mode == 1) return launch_t<D, CAUSAL, true, false, false, false>(p, s);
   if (mode == 3) return launch_t<D, CAUSAL, true, false, false, true>(p, s);
   return launch_t<D, CAUSAL, true, true, false, false>(p, s);
 }
@@ -1317,8 +1836,8 @@ static int launch_c_weighted(const FwdParams& p, int mode, hipStream_t s) {
       if (mode == 1) return launch_t<D, CAUSAL, true, false, true, false, true>(p, s);
       return launch_t<D, CAUSAL, true, true, true, false, true>(p, s);
     }
+    if (mode == 1) return launch_t<D, CAUSAL, true, false, true, false>(p, s);
   }
-  if (mode == 1) return launch_t<D, CAUSAL, true, false, true, false>(p, s);
   if (mode == 3) return launch_t<D, CAUSAL, true, false, true, true>(p, s);
   return launch_t<D, CAUSAL, true, true, true, false>(p, s);
 }
@@ -1335,9 +1854,26 @@ static int launch_d_weighted(const FwdParams& p, bool causal, int mode, hipStrea
 
 // the d = 128 forward kernels without the weighted check (part 1)
 int launch_d128_plain(const FwdParams& p, bool causal, int mode, hipStream_t s);
+// the d = 256 forward kernels (part 2)
+int launch_d256(const FwdParams& p, bool causal, int mode, hipStream_t s);
 #if FABFT_PART == 1
 int launch_d128_plain(const FwdParams& p, bool causal, int mode, hipStream_t s) {
   return launch_d_plain<128>(p, causal, mode, s);
+}
+#elif FABFT_PART == 2
+template <bool CHECK, bool WCHK>
+static int launch_wide(const FwdParams& p, bool causal, hipStream_t s) {
+  (void)hipGetLastError();
+  const dim3 grid(p.grid), block(Cfg<256>::THREADS);
+  if (causal) hipLaunchKernelGGL((wide_kernel<true, CHECK, WCHK>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((wide_kernel<false, CHECK, WCHK>), grid, block, 0, s, p);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_d256(const FwdParams& p, bool causal, int mode, hipStream_t s) {
+  if (mode == 0) return launch_wide<false, false>(p, causal, s);
+  if (mode == 1) return p.wcheck ? launch_wide<true, true>(p, causal, s) : launch_wide<true, false>(p, causal, s);
+  return p.wcheck ? launch_d_weighted<256>(p, causal, mode, s) : launch_d_plain<256>(p, causal, mode, s);
 }
 #else
 template <int D>
@@ -1694,7 +2230,7 @@ int launch_fwd(const FwdParams& p, int d, bool causal, int mode, hipStream_t str
     if (dc == 128) return launch_decode<128>(p, causal, stream);
     return launch_decode<64>(p, causal, stream);
   }
-  if (dc == 256) return launch_d<256>(p, causal, mode, stream);
+  if (dc == 256) return launch_d256(p, causal, mode, stream);
   if (dc == 128) return launch_d<128>(p, causal, mode, stream);
   return launch_d<64>(p, causal, mode, stream);
 }
