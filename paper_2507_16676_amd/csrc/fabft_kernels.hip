@@ -247,10 +247,13 @@ struct Tile {
   static constexpr int CPR = D / 8;
   // (at d >= 128 a row spans all 64 banks or twice that, at d = 64 half of
   // them)
+  // At d = 96 a row takes 48 banks: rows 4 apart start on the same bank, and
+  // the rows in between 16 banks (4 chunks) apart, so the K swizzle only has to
+  // part rows 4 apart and V needs none.
   // K: 16 lanes read 16 different rows at one logical chunk
-  static __device__ __forceinline__ int kswz(int r) { return D >= 128 ? (r & 15) : ((r >> 1) & 7); }
+  static __device__ __forceinline__ int kswz(int r) { return D == 96 ? (r >> 2) & 3 : D >= 128 ? (r & 15) : ((r >> 1) & 7); }
   // V: 32 lanes read 4 consecutive rows x 4 consecutive chunks
-  static __device__ __forceinline__ int vswz(int r) { return D >= 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1); }
+  static __device__ __forceinline__ int vswz(int r) { return D == 96 ? 0 : D >= 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1); }
   static __device__ __forceinline__ int kidx(int r, int c) { return r * D + 8 * (c ^ kswz(r)); }
   static __device__ __forceinline__ int vidx(int r, int c) { return r * D + 8 * (c ^ vswz(r)); }
 };
@@ -374,8 +377,14 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
   constexpr int NKB = BC / 32;    // 32-key blocks per tile
   constexpr int NDB = D / 32;     // 32-column blocks of the output
   constexpr int NDS = D / 16;     // 16-wide steps over d in Q K^T
-  constexpr int NLD = BC * CPR / kThreads;   // 16-byte loads per thread per tensor and tile
-  static_assert(NLD >= 1 && BC * CPR == NLD * kThreads, "loads cover the tile");
+  // 16-byte loads per thread of a tile's K and V together, and per tensor; at
+  // d = 96 (one and a half per tensor) the second of three is K's for the
+  // first half of the waves and V's for the second
+  constexpr int LPT = 2 * BC * CPR / kThreads;
+  constexpr bool kOdd = LPT % 2 != 0;
+  constexpr int NLD = LPT / 2;
+  static_assert(NLD >= 1 && 2 * BC * CPR == LPT * kThreads && (!kOdd || (LPT == 3 && !TWOPASS)),
+                "loads cover the tile");
   // a workgroup may run a list of items (p.persist), handing the LDS ring
   // from one item to the next: the next item's Q and first key tiles load
   // while the current item's last tiles and epilogue run
@@ -411,7 +420,7 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
   const int off = Lk - Lq;
   // q, k, v, o rows hold DIO <= D columns in memory; on chip the rows are D
   // wide and columns DIO.. are zero (zero scores, zero outputs)
-  const int DIO = p.dio;
+  const int DIO = D == 96 ? 96 : p.dio;
   const int CIO = DIO / 8;   // 16-byte chunks per row in memory
   const uint32_t kv_bytes = (uint32_t)Lk * DIO * 2;
   // key tiles of query tile qt_ (keys [0, kend)); wave-uniform (the
@@ -502,7 +511,7 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
   // ---- loader: 16-byte slot j*512 + tid of a tile holds row slot/CPR, stored
   // chunk slot%CPR (logical chunk = stored ^ swz(row)); rows past Lk read as
   // zeros (the mask gives them weight 0)
-  uint32_t kvo[NLD], vvo[NLD];
+  uint32_t kvo[NLD + (kOdd ? 1 : 0)], vvo[NLD];
 #pragma unroll
   for (int j = 0; j < NLD; ++j) {
     const int slot = j * kThreads + tid;
@@ -512,6 +521,15 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
     const int kc = sc ^ Tile<D>::kswz(row), vc = sc ^ Tile<D>::vswz(row);
     kvo[j] = kc < CIO ? (uint32_t)(row * DIO + 8 * kc) * 2 : kv_bytes;
     vvo[j] = vc < CIO ? (uint32_t)(row * DIO + 8 * vc) * 2 : kv_bytes;
+  }
+  if constexpr (kOdd) {
+    // slots of K then V: threads of the second half of the waves hold V's
+    // first slots in load 1 (kvo[1]), all threads V's others in load 2 (vvo[0])
+    const bool isv = wave >= kWaves / 2;
+    const int s1 = isv ? tid - kThreads / 2 : kThreads + tid;
+    const int r1 = s1 / CPR, c1 = s1 % CPR, s2 = kThreads / 2 + tid, r2 = s2 / CPR, c2 = s2 % CPR;
+    kvo[1] = (uint32_t)(r1 * DIO + 8 * (c1 ^ (isv ? Tile<D>::vswz(r1) : Tile<D>::kswz(r1)))) * 2;
+    vvo[0] = (uint32_t)(r2 * DIO + 8 * (c2 ^ Tile<D>::vswz(r2))) * 2;
   }
   // LDS byte address of the ring and of this wave's 1 KiB slot in a tile
   const uint32_t ring_lds = (uint32_t)(uintptr_t)(lds_void*)&ring;
@@ -535,11 +553,19 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
     // (scalar adds) rather than hoisted as one live SGPR per stage and load
     uint32_t wl = wave_lds;
     asm volatile("" : "+s"(wl));
+    constexpr uint32_t kOff = offsetof(Ring<D>, k) + S * sizeof(Ring<D>::k[0]);
+    constexpr uint32_t vOff = offsetof(Ring<D>, v) + S * sizeof(Ring<D>::v[0]);
+    if constexpr (kOdd) {
+      constexpr uint32_t kHalf = kThreads * 8;   // half of the workgroup's 16-byte slots
+      const bool isv = wave >= kWaves / 2;
+      buffer_load_lds16(kr, kvo[0], soff, wl + kOff);
+      buffer_load_lds16(isv ? vr : kr, kvo[1], soff, wl + (isv ? vOff - kHalf : kOff + 2 * kHalf));
+      buffer_load_lds16(vr, vvo[0], soff, wl + vOff + kHalf);
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < NLD; ++j) {
       // each wave writes its own contiguous 1 KiB of the stage
-      constexpr uint32_t kOff = offsetof(Ring<D>, k) + S * sizeof(Ring<D>::k[0]);
-      constexpr uint32_t vOff = offsetof(Ring<D>, v) + S * sizeof(Ring<D>::v[0]);
       buffer_load_lds16(kr, kvo[j], soff, wl + kOff + j * kThreads * 16);
       if (!TWOPASS || pass != 0) buffer_load_lds16(vr, vvo[j], soff, wl + vOff + j * kThreads * 16);
     }
@@ -566,14 +592,14 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
     float a = 0.f, aw = 0.f;
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
-      // at d = 128: chunk part + 4 i. A 16-lane read pass covers keys
+      // at d = 128 (and 96): chunk part + 4 i. A 16-lane read pass covers keys
       // 4m .. 4m+3 (parts 0-3 each); the V swizzle stores logical chunk c of
       // key r at c ^ 4(r mod 4), so the pass reads 16 distinct chunks of the
       // 256-byte rows: no bank conflict. At d = 64: chunk part + 4 j,
       // j = i ^ (key mod 2), so that the keys of one pass take opposite
       // halves of the row, whose banks the V swizzle keeps apart. d = 256
       // reads CPT consecutive chunks.
-      const int c = D == 128 ? part + TPK * i
+      const int c = D == 128 || D == 96 ? part + TPK * i
                   : CPT == 2 ? part + TPK * (i ^ (key & 1)) : CPT * part + i;
       const u32x4 ch = *reinterpret_cast<const u32x4*>(&sv[Tile<D>::vidx(key, c)]);
 #pragma unroll
@@ -918,7 +944,6 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
   };
 
   // ---- pipeline: AHEAD tiles loading while tile t is processed
-  constexpr int LPT = 2 * NLD;   // loads per thread per tile (K and V)
   // wait until at most n (0 .. AHEAD-1) tiles of this wave's loads are in flight
   auto wait_tiles = [&](int n) __attribute__((always_inline)) {
     if constexpr (TWOPASS) {
@@ -1174,7 +1199,8 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
           const int lim = wq_lo + off + 1;   // tiles wholly below the wave's diagonal
           tw = min(tw, lim <= 0 ? 0 : lim / BC);
         }
-        const size_t kro = ((size_t)bh * (p.ntk + 1) + tw) * D;
+        // (rows of the prefix hold compute_width(d) floats)
+        const size_t kro = ((size_t)bh * (p.ntk + 1) + tw) * (D == 96 ? 128 : D);
         float rhs = 0.f, ms = 0.f;
 #pragma unroll
         for (int s2 = 0; s2 < NDS; ++s2) {
@@ -1810,6 +1836,11 @@ static int launch_t(const FwdParams& p0, hipStream_t stream) {
 // instantiations, below
 template <int D, bool CAUSAL>
 static int launch_c(const FwdParams& p, int mode, hipStream_t s) {
+  if constexpr (D == 96) {
+    if (mode == 0) return launch_t<D, CAUSAL, false, false, false, false>(p, s);
+    if (p.kpre) return launch_t<D, CAUSAL, true, false, false, false, true>(p, s);
+    return launch_t<D, CAUSAL, true, false, false, false>(p, s);
+  } else {
   if constexpr (D != 256) {   // wide_kernel runs modes 0 and 1 at d = 256
     if (mode == 0) return launch_t<D, CAUSAL, false, false, false, false>(p, s);
   }
@@ -1825,10 +1856,15 @@ static int launch_c(const FwdParams& p, int mode, hipStream_t s) {
   }
   if (mode == 3) return launch_t<D, CAUSAL, true, false, false, true>(p, s);
   return launch_t<D, CAUSAL, true, true, false, false>(p, s);
+  }
 }
 
 template <int D, bool CAUSAL>
 static int launch_c_weighted(const FwdParams& p, int mode, hipStream_t s) {
+  if constexpr (D == 96) {
+    if (p.kpre) return launch_t<D, CAUSAL, true, false, true, false, true>(p, s);
+    return launch_t<D, CAUSAL, true, false, true, false>(p, s);
+  } else {
   if (mode == 4) return launch_t<D, CAUSAL, true, false, true, false, false, true>(p, s);
   if (mode == 5) return launch_t<D, CAUSAL, true, true, true, false, false, true>(p, s);
   if constexpr (D != 256) {
@@ -1840,6 +1876,7 @@ static int launch_c_weighted(const FwdParams& p, int mode, hipStream_t s) {
   }
   if (mode == 3) return launch_t<D, CAUSAL, true, false, true, true>(p, s);
   return launch_t<D, CAUSAL, true, true, true, false>(p, s);
+  }
 }
 
 template <int D>
@@ -1854,11 +1891,16 @@ static int launch_d_weighted(const FwdParams& p, bool causal, int mode, hipStrea
 
 // the d = 128 forward kernels without the weighted check (part 1)
 int launch_d128_plain(const FwdParams& p, bool causal, int mode, hipStream_t s);
+// d = 96 at its own width (modes 0 and 1 without the weighted check; part 1)
+int launch_d96_plain(const FwdParams& p, bool causal, int mode, hipStream_t s);
 // the d = 256 forward kernels (part 2)
 int launch_d256(const FwdParams& p, bool causal, int mode, hipStream_t s);
 #if FABFT_PART == 1
 int launch_d128_plain(const FwdParams& p, bool causal, int mode, hipStream_t s) {
   return launch_d_plain<128>(p, causal, mode, s);
+}
+int launch_d96_plain(const FwdParams& p, bool causal, int mode, hipStream_t s) {
+  return launch_d_plain<96>(p, causal, mode, s);
 }
 #elif FABFT_PART == 2
 template <bool CHECK, bool WCHK>
@@ -2231,6 +2273,13 @@ int launch_fwd(const FwdParams& p, int d, bool causal, int mode, hipStream_t str
     return launch_decode<64>(p, causal, stream);
   }
   if (dc == 256) return launch_d256(p, causal, mode, stream);
+  // d = 96: the forward runs at its own width, a quarter less matrix, LDS and
+  // memory work than on rows zero-padded to 128, bitwise the same result
+  // (causal B=2 H=32 L=2048: 73.3 -> 64.2 us with the checksum, 69.8 -> 62.9
+  // without). The debug, two-pass and split kernels keep the padded rows.
+  if (d == 96 && mode <= 1)
+    return p.wcheck && mode == 1 ? launch_d_weighted<96>(p, causal, mode, stream)
+                                 : launch_d96_plain(p, causal, mode, stream);
   if (dc == 128) return launch_d<128>(p, causal, mode, stream);
   return launch_d<64>(p, causal, mode, stream);
 }
