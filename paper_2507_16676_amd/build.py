@@ -43,6 +43,11 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
 # (needs relaxed NaN rules; the kernels test non-finite values on the bits and
 # a NaN score still reaches exp2 and propagates into o, l and c).
 KERNEL_FLAGS = ["-mno-amdgpu-ieee", "-fno-honor-nans",
+                # MFMA results in vector registers first, so that kernels that
+                # may use more than 256 registers (one wave per SIMD) do not
+                # copy scores and outputs through the accumulation registers;
+                # the code of the others does not change
+                "-mllvm", "-amdgpu-mfma-vgpr-form=1",
                 # the two-pass kernels unroll their loop over the two passes
                 # (each pass then has constant branches); the injection forms
                 # of that loop exceed LLVM's default size limit for a requested
@@ -52,10 +57,9 @@ KERNEL_FLAGS = ["-mno-amdgpu-ieee", "-fno-honor-nans",
 
 # The kernel source is compiled three times (FABFT_PART 0 to 2, see its head):
 # part 1, the d = 128 forward kernels without the weighted check, with LLVM's
-# iterative ILP scheduler; part 2, the d = 256 forward kernels, with MFMA
-# results in vector registers first.
+# iterative ILP scheduler; part 2, the d = 256 forward kernels.
 PART1_FLAGS = ["-DFABFT_PART=1", "-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]
-PART2_FLAGS = ["-DFABFT_PART=2", "-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+PART2_FLAGS = ["-DFABFT_PART=2"]
 
 
 def build_cmds(out: str, objdir: str, extra=()) -> list[list[str]]:

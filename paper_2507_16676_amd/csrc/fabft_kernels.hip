@@ -274,12 +274,12 @@ enum { kRowVsHi = 0, kRowVsLo = 1, kRowOnes = 2, kRowZero = 3, kRowWHi = 4, kRow
 // stage a compile-time constant, every operand read of a tile is a per-lane
 // base register plus an immediate offset (K and V stages each span 64 KiB at
 // d = 128, the reach of the LDS offset field).
-template <int D>
+template <int D, int STAGES = Cfg<D>::STAGES>
 struct Ring {
   static constexpr int VS = D == 256 ? kBc : kBc + 8;   // vsm row stride (keys)
-  uint16_t k[Cfg<D>::STAGES][kBc * D];
-  uint16_t v[Cfg<D>::STAGES][kBc * D];
-  uint16_t vsm[Cfg<D>::STAGES][kVsmRows][VS];
+  uint16_t k[STAGES][kBc * D];
+  uint16_t v[STAGES][kBc * D];
+  uint16_t vsm[STAGES][kVsmRows][VS];
 };
 
 // ---- work items: (head bh, query tile qt) pairs, p.n_items of them.
@@ -364,14 +364,19 @@ struct StageId {
 // SCHK: the score check is compiled in (only with CHECK, not with SPLIT).
 // TWOPASS: Algorithm 1 hosts the checksum: a first pass over K takes each
 // row's max, the second runs the loop with that max fixed (only with CHECK).
+// HALFWG: workgroups of half the waves and query rows (half_is_faster). At
+// d = 64 (96) three (two) of them fit on a CU with a three-stage ring: two
+// tiles ahead rather than three, and the CU's other workgroups fill the waits.
 template <int D, bool CAUSAL, bool CHECK, bool INJECT, bool WCHK, bool SPLIT, bool SCHK = false,
-          bool TWOPASS = false>
-__global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
-  constexpr int kWaves = Cfg<D>::WAVES;
-  constexpr int kThreads = Cfg<D>::THREADS;
-  constexpr int kBr = Cfg<D>::BR;
-  constexpr int kStages = Cfg<D>::STAGES;
-  constexpr int AHEAD = Cfg<D>::AHEAD;
+          bool TWOPASS = false, bool HALFWG = false>
+__global__ __launch_bounds__(Cfg<D>::THREADS / (HALFWG ? 2 : 1), HALFWG && D <= 96 ? (D == 64 ? 3 : 2) : 1)
+void fwd_kernel(FwdParams p) {
+  constexpr int kWaves = Cfg<D>::WAVES / (HALFWG ? 2 : 1);
+  constexpr int kThreads = 64 * kWaves;
+  constexpr int kBr = 32 * kWaves;
+  constexpr int kStages = HALFWG && D <= 96 ? 3 : Cfg<D>::STAGES;
+  constexpr int AHEAD = kStages - 1;
+  using RingT = Ring<D, kStages>;
   constexpr int BC = kBc;
   constexpr int CPR = Tile<D>::CPR;
   constexpr int NKB = BC / 32;    // 32-key blocks per tile
@@ -388,9 +393,9 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
   // a workgroup may run a list of items (p.persist), handing the LDS ring
   // from one item to the next: the next item's Q and first key tiles load
   // while the current item's last tiles and epilogue run
-  constexpr bool kPersist = !INJECT && !SPLIT && !SCHK && !TWOPASS && Cfg<D>::AHEAD >= 3;
+  constexpr bool kPersist = !INJECT && !SPLIT && !SCHK && !TWOPASS && !HALFWG && Cfg<D>::AHEAD >= 3;
 
-  __shared__ __attribute__((aligned(16))) Ring<D> ring;
+  __shared__ __attribute__((aligned(16))) RingT ring;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -553,8 +558,8 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
     // (scalar adds) rather than hoisted as one live SGPR per stage and load
     uint32_t wl = wave_lds;
     asm volatile("" : "+s"(wl));
-    constexpr uint32_t kOff = offsetof(Ring<D>, k) + S * sizeof(Ring<D>::k[0]);
-    constexpr uint32_t vOff = offsetof(Ring<D>, v) + S * sizeof(Ring<D>::v[0]);
+    constexpr uint32_t kOff = offsetof(RingT, k) + S * sizeof(RingT::k[0]);
+    constexpr uint32_t vOff = offsetof(RingT, v) + S * sizeof(RingT::v[0]);
     if constexpr (kOdd) {
       constexpr uint32_t kHalf = kThreads * 8;   // half of the workgroup's 16-byte slots
       const bool isv = wave >= kWaves / 2;
@@ -587,7 +592,7 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
       if (wave >= SW) return;                     // wave-uniform
     }
     const uint16_t* const sv = ring.v[S];
-    uint16_t(*const svsm)[Ring<D>::VS] = ring.vsm[S];
+    uint16_t(*const svsm)[RingT::VS] = ring.vsm[S];
     const int key = tid / TPK, part = tid % TPK;
     float a = 0.f, aw = 0.f;
 #pragma unroll
@@ -630,7 +635,7 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
     constexpr int S = decltype(S_)::value;
     const uint16_t* const sk = ring.k[S];
     const uint16_t* const sv = ring.v[S];
-    const uint16_t(*const svsm)[Ring<D>::VS] = ring.vsm[S];
+    const uint16_t(*const svsm)[RingT::VS] = ring.vsm[S];
     const int kv0 = t * BC;
     const bool need_mask = (kv0 + BC > Lk) || (CAUSAL && kv0 + BC - 1 > wq_lo + off);
 
@@ -1037,6 +1042,10 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
           if constexpr (CHECK) {
             if (pass == 1) sumrow(StageId<0>());
           }
+        } else if constexpr (AHEAD == 2) {
+          wait_tiles(min(1, t_end - 1 - t_lo));
+          __syncthreads();
+          if constexpr (CHECK) sumrow(StageId<0>());
         }
       }
       // A use of Q here, on every path into the loop, puts the compiler's own
@@ -1044,7 +1053,8 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
       // also waits for the first tiles) before the loop rather than inside it.
 #pragma unroll
       for (int s = 0; s < NDS; ++s) asm volatile("" : : "v"(qf[s]));
-      static_assert(kStages == 4 || kStages == 2, "the loop below is unrolled over the stages");
+      static_assert(kStages == 4 || kStages == 2 || (kStages == 3 && !TWOPASS && !INJECT),
+                    "the loop below is unrolled over the stages");
       static_assert(AHEAD == kStages - 1, "the stage of tile t-1 takes tile t+AHEAD");
       auto step = [&](auto S_, int t) __attribute__((always_inline)) {
         constexpr int S = decltype(S_)::value;
@@ -1053,6 +1063,13 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
           // barrier every wave is done with tile t-1, whose stage takes tile t+3
           wait_tiles(min(1, te_v - 2 - t));
           __syncthreads();
+        } else if constexpr (AHEAD == 2) {
+          // tile t+1 complete; after the barrier every wave is done with tile
+          // t-1, whose stage takes tile t+2 (a step to arrive in, which the
+          // other workgroups of the CU fill)
+          wait_tiles(0);
+          __syncthreads();
+          issue(StageId<(S + 2) % kStages>(), t + 2);
         } else {
           // tile t complete; after the barrier every wave is done with tile t-1,
           // whose stage takes tile t+1, loading while tile t is processed
@@ -1098,15 +1115,21 @@ __global__ __launch_bounds__(Cfg<D>::THREADS, 1) void fwd_kernel(FwdParams p) {
           if constexpr (CHECK) {
             if (t + 1 < te_v && pass == 1) sumrow(StageId<(S + 1) % kStages>());
           }
+        } else if constexpr (AHEAD == 2) {
+          if constexpr (CHECK) {
+            if (t + 1 < t_end) sumrow(StageId<(S + 1) % kStages>());
+          }
         }
       };
       for (int t = t_lo; t < t_end; t += kStages) {
         step(StageId<0>(), t);
         if (t + 1 >= t_end) break;
         step(StageId<1>(), t + 1);
-        if constexpr (kStages == 4) {
+        if constexpr (kStages >= 3) {
           if (t + 2 >= t_end) break;
           step(StageId<2 % kStages>(), t + 2);
+        }
+        if constexpr (kStages == 4) {
           if (t + 3 >= t_end) break;
           step(StageId<3 % kStages>(), t + 3);
         }
@@ -1801,23 +1824,72 @@ static int device_cus(hipStream_t stream) {
   return n;
 }
 
+// Whether workgroups of half the waves (128 query rows) run a forward faster
+// than those of p.n_items' 256 rows on `cus` compute units. A wave alone on its
+// SIMD takes about 0.7 of the time per key tile that two take together, and
+// at d = 64 (96) three (two) half workgroups share a CU, none of them in step
+// with the others, so that one's start-up and epilogue overlap another's
+// products. Measured (us, full -> half workgroups, checksum on):
+//  * every half workgroup has a CU of its own: d = 64, 32 heads of 512: 14.5 ->
+//    11.0; d = 96, 32 heads of 256, causal: 10.4 -> 8.2; d = 128: 13.3 -> 10.1.
+//    At d = 128 with at most 128 query rows there is nothing to spread and
+//    the idle waves' share of the loads is missed (4,096 keys: 86 -> 96).
+//  * no more full workgroups than CUs, causal: a light query tile shares the
+//    CU of a heavy one (L = 2048, 32 heads: d = 64 42 -> 35, 96 49 -> 44,
+//    128 59 -> 56; L = 1500: 32 -> 26, 37 -> 31, 44 -> 35), but not with
+//    short rows (L = 1024, 64 heads: 23.8 -> 24.5, 28.0 -> 29.5, level). Without a
+//    mask two half workgroups do the work of one full one in the same time
+//    (d = 64, 64 heads of 1,024: 25.7 -> 26.6; of 512: 17.3 -> 16.8).
+//  * more than that: d = 64 without a mask gains by its three workgroups per
+//    CU at any length (384 heads of 512: 42.6 -> 40.4, of 300: 30.8 -> 23.9;
+//    96 heads of 4,096: 481 -> 468); with the causal order long rows lose (32
+//    heads of 4,096: 91 -> 109) and short ones gain (L = 700: 33 -> 21). At
+//    d = 96 short rows gain (384 heads of 512: 59.9 -> 58.9, of 128: 23.3 ->
+//    19.3), at d = 128 (one half workgroup per CU: its LDS ring) none do.
+template <int D, bool CAUSAL>
+static bool half_is_faster(const FwdParams& p, int cus) {
+  constexpr int kRows = query_tile_for(D) / 2;
+  const long long full = p.n_items;
+  const long long half = full / p.n_qt * ((p.Lq + kRows - 1) / kRows);
+  const int tiles = (p.Lk + kBc - 1) / kBc;   // of the last query tile
+  // query tiles of about the same work: no mask, or few queries over many keys
+  const bool flat = !CAUSAL || 2LL * (p.Lk - p.Lq + 2 * kRows) >= p.Lk;
+  if (cus <= 0) return false;
+  if (half <= cus) return D != 128 || half > full;
+  if (full <= cus) return flat ? D == 64 && tiles <= 8 : tiles >= 20;
+  if (D == 128) return false;
+  if (D == 64 && flat) return half <= INT_MAX;
+  return tiles <= (D == 64 ? 12 : 8) && half <= INT_MAX;
+}
+
 template <int D, bool CAUSAL, bool CHECK, bool INJECT, bool WCHK, bool SPLIT, bool SCHK = false,
           bool TWOPASS = false>
 static int launch_t(const FwdParams& p0, hipStream_t stream) {
   FwdParams p = p0;
   p.persist = 0;
-  if constexpr (!INJECT && !SPLIT && !SCHK && !TWOPASS && Cfg<D>::AHEAD >= 3) {
+  if constexpr (!INJECT && !SPLIT && !TWOPASS && D != 256) {
+    const int cus = device_cus(stream);
+    const int mode = g_persist.load();
+    if (mode != kPersistAlways && half_is_faster<D, CAUSAL>(p, cus)) {
+      constexpr int kRows = query_tile_for(D) / 2;
+      const int heads = p.n_items / p.n_qt;
+      p.n_qt = (p.Lq + kRows - 1) / kRows;
+      p.grid = p.n_items = heads * p.n_qt;
+      (void)hipGetLastError();   // as below
+      hipLaunchKernelGGL((fwd_kernel<D, CAUSAL, CHECK, INJECT, WCHK, SPLIT, SCHK, TWOPASS, true>),
+                         dim3(p.grid), dim3(Cfg<D>::THREADS / 2), 0, stream, p);
+      return hipGetLastError() == hipSuccess ? 0 : -1;
+    }
     // one workgroup per CU (the occupancy the launch bounds give), a
     // multiple of 8 so that workgroup b stays on XCD b mod 8; with the mask
     // only for a head count divisible by 8 (the banded schedule). Automatic
     // only for short rows (at most 16 key tiles), where a workgroup's
     // start-up is a large part of its work; measured neutral on long rows.
-    const int g = device_cus(stream) & ~7;
+    const int g = cus & ~7;
     const int heads = p.n_items / p.n_qt;
-    const int mode = g_persist.load();
     const bool want = mode == kPersistAlways ||
                       (mode == kPersistAuto && (p.Lk + kBc - 1) / kBc <= 16);
-    if (want && g >= 8 && p.n_items > g && (!CAUSAL || (heads & 7) == 0)) {
+    if (!SCHK && want && g >= 8 && p.n_items > g && (!CAUSAL || (heads & 7) == 0)) {
       p.persist = 1;
       p.grid = g;
     }

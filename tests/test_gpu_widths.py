@@ -1,7 +1,7 @@
 """The forward kernels that differ from the debug kernel's form (d = 256: the
 next tile's scores taken beside this tile's softmax; d = 96: rows at their own
-width on chip instead of zero-padded to 128) against the debug kernel: every
-row runs the same operations in the same order, so O, resid and flags are
+width on chip instead of zero-padded to 128; launches in half workgroups of 128
+query rows at d = 64, 96 and 128) against the debug kernel: every row runs the same operations in the same order, so O, resid and flags are
 bitwise equal, at the edges of the query and key tiles, for waves without keys
 or rows, with peaked keys (rescales) and with each check."""
 import pytest
@@ -20,7 +20,33 @@ SHAPES = [(1, 1, True), (33, 64, False), (128, 65, True), (129, 128, True), (127
           (257, 192, True), (300, 300, True), (64, 320, False), (31, 257, True), (256, 256, True)]
 
 
-@pytest.mark.parametrize("d", [96, 256])
+def _same(a, b):
+    return torch.equal(a.view(torch.int16), b.view(torch.int16)) if a.dtype == torch.bfloat16 \
+        else torch.equal(a.view(torch.int32), b.view(torch.int32)) if a.dtype == torch.float32 \
+        else torch.equal(a, b)
+
+
+@pytest.mark.parametrize("d", [64, 96, 128])
+@pytest.mark.parametrize("H,Lq,Lk,causal", [
+    (32, 1500, 1500, True),     # no more full workgroups than CUs, causal
+    (64, 1024, 1024, True),     # the same with short rows: full workgroups
+    (300, 130, 300, False),     # more than that, short rows
+    (150, 300, 1100, False),    # more than that, 18 key tiles, no mask
+    (270, 200, 700, True),      # more than that, query tiles of about equal work
+])
+def test_launch_shapes_match_debug_kernel(H, Lq, Lk, causal, d):
+    print(f"[shapes] d{d} H{H} Lq{Lq} Lk{Lk} causal={causal}", flush=True)
+    w = W.Workload("shapes", 1, H, Lq, Lk, d, causal, d ** -0.5, peaked_frac=0.01, seed=Lq + Lk)
+    q, k, v = G.dev_inputs(W.make_inputs(w))
+    o, r, f = F.attn_fwd(q, k, v, causal=causal, scale=w.scale)
+    off = F.attn_fwd(q, k, v, causal=causal, scale=w.scale, check=False)
+    od, rd, fd, _, _ = F.attn_fwd_inject(q, k, v, causal=causal, scale=w.scale)
+    torch.cuda.synchronize()
+    assert _same(o, od) and _same(r, rd) and _same(f, fd) and _same(o, off)
+    assert int((f != 0).sum()) == 0
+
+
+@pytest.mark.parametrize("d", [64, 96, 128, 256])
 @pytest.mark.parametrize("Lq,Lk,causal", SHAPES)
 def test_forward_matches_debug_kernel(Lq, Lk, causal, d):
     print(f"[widths] d{d} Lq{Lq} Lk{Lk} causal={causal}", flush=True)
@@ -44,10 +70,8 @@ def test_forward_matches_debug_kernel(Lq, Lk, causal, d):
         finally:
             F.set_weighted_check(False)
             F.set_score_check(None)
-        assert torch.equal(o.view(torch.int16), od.view(torch.int16)), check
-        assert torch.equal(r.view(torch.int32), rd.view(torch.int32)), check
-        assert torch.equal(f, fd), check
+        assert _same(o, od) and _same(r, rd) and _same(f, fd), check
         assert int((f != 0).sum()) == 0, check
-        assert torch.equal(o.view(torch.int16), off.view(torch.int16)), check
+        assert _same(o, off), check
     err = abs(G.from_dev_bf16(o) - G.oracle_rows(inp, causal, w.scale)["O"])
     assert err.max() <= G.O_MAX_ABS
