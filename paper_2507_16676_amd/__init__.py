@@ -17,6 +17,7 @@ contiguity and device before the library sees its pointer.
 from __future__ import annotations
 
 import ctypes
+import functools
 import math
 import os
 from dataclasses import dataclass
@@ -52,11 +53,14 @@ class FabftDebugOut(ctypes.Structure):
 
 
 _LIB = None
+# set by _load: torch, and the raw handle of a device's current stream
+_torch = None
+_raw_stream = None
 
 
 def _load() -> ctypes.CDLL:
     """Load libfabft.so once; raise if it is not built (no CPU fallback)."""
-    global _LIB
+    global _LIB, _torch, _raw_stream
     if _LIB is not None:
         return _LIB
     if not os.path.exists(LIB_PATH):
@@ -67,7 +71,11 @@ def _load() -> ctypes.CDLL:
     # that same runtime (the one that owns torch's memory and streams); loaded
     # before torch, it would pull in the system runtime instead and launches
     # on torch's streams fail
-    import torch  # noqa: F401
+    import torch
+    _torch = torch
+    # the handle without a Stream object around it (0.2 against 1.5 us)
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+        lambda index: torch.cuda.current_stream(index).cuda_stream)
     L = ctypes.CDLL(LIB_PATH)
     L.fabft_attn_fwd.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _i, _i, _i, _i, _i, _i, _f]
     L.fabft_attn_fwd.restype = _i
@@ -254,28 +262,30 @@ def query_tile(d: int = 128) -> int:
 
 
 def _shape(q, k, v):
-    import torch
+    if _torch is None:
+        _load()
+    bf16 = _torch.bfloat16
     for name, t in (("q", q), ("k", k), ("v", v)):
-        if t.dtype != torch.bfloat16:
+        if t.dtype is not bf16:
             raise TypeError(f"{name} must be torch.bfloat16, got {t.dtype}")
         if not t.is_cuda:
             raise ValueError(f"{name} must be on the GPU")
         if t.dim() != 4 or not t.is_contiguous():
             raise ValueError(f"{name} must be a contiguous [B, H, L, d] tensor")
     B, H, Lq, d = q.shape
-    if tuple(k.shape[:2]) != (B, H) or k.shape[3] != d or tuple(v.shape) != tuple(k.shape):
+    ks = k.shape
+    if ks[0] != B or ks[1] != H or ks[3] != d or v.shape != ks:
         raise ValueError(f"shape mismatch: q {tuple(q.shape)} k {tuple(k.shape)} v {tuple(v.shape)}")
-    return B, H, Lq, k.shape[2], d
+    return B, H, Lq, ks[2], d
 
 
 def _check_out(t, name: str, shape, dtype, device):
     """A caller-supplied tensor must have exactly this shape and dtype, be
     contiguous and sit on `device`: the library only sees its pointer and
     would write past the end of a short or mistyped buffer."""
-    import torch
-    if not isinstance(t, torch.Tensor):
+    if not isinstance(t, _torch.Tensor):
         raise ValueError(f"{name} must be a torch tensor")
-    if tuple(t.shape) != tuple(shape) or t.dtype != dtype:
+    if t.shape != shape or t.dtype is not dtype:
         raise ValueError(f"{name} must be {dtype} of shape {tuple(shape)}, got {t.dtype} "
                          f"{tuple(t.shape)}")
     if not t.is_contiguous():
@@ -287,8 +297,7 @@ def _check_out(t, name: str, shape, dtype, device):
 
 def _check_workspace(t, name: str, need: int, device):
     """A workspace: a contiguous tensor on `device` of at least `need` bytes."""
-    import torch
-    if not isinstance(t, torch.Tensor):
+    if not isinstance(t, _torch.Tensor):
         raise ValueError(f"{name} must be a torch tensor")
     if not t.is_contiguous() or t.device != device:
         raise ValueError(f"{name} must be a contiguous tensor on {device}")
@@ -298,8 +307,14 @@ def _check_workspace(t, name: str, need: int, device):
 
 
 def _stream(dev):
-    import torch
-    _load().fabft_set_stream(ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream))
+    _LIB.fabft_set_stream(_raw_stream(dev.index))
+
+
+def _outputs(q, B: int, H: int, Lq: int):
+    """New o, resid and flags for the queries q."""
+    dev = q.device
+    return (_torch.empty_like(q), _torch.empty((B, H, Lq), dtype=_torch.float32, device=dev),
+            _torch.empty((B, H, Lq), dtype=_torch.uint8, device=dev))
 
 
 def attn_fwd(q, k, v, causal: bool = False, scale: float | None = None, check: bool = True,
@@ -308,29 +323,27 @@ def attn_fwd(q, k, v, causal: bool = False, scale: float | None = None, check: b
 
     out: optional preallocated (o[, resid, flags]) tensors to write into.
     """
-    import torch
     B, H, Lq, Lk, d = _shape(q, k, v)
     scale = 1.0 / math.sqrt(d) if scale is None else float(scale)
     dev = q.device
     if out is not None:
         if len(out) not in (1, 3) or (check and len(out) != 3):
             raise ValueError("out must be (o,) with check=False, or (o, resid, flags)")
-        o = _check_out(out[0], "out[0] (o)", q.shape, torch.bfloat16, dev)
+        o = _check_out(out[0], "out[0] (o)", q.shape, _torch.bfloat16, dev)
+        if check:
+            resid = _check_out(out[1], "out[1] (resid)", (B, H, Lq), _torch.float32, dev)
+            flags = _check_out(out[2], "out[2] (flags)", (B, H, Lq), _torch.uint8, dev)
+    elif check:
+        o, resid, flags = _outputs(q, B, H, Lq)
     else:
-        o = torch.empty_like(q)
+        o = _torch.empty_like(q)
     _stream(dev)
     if not check:
-        _check(_load().fabft_attn_fwd_nocheck(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
+        _check(_LIB.fabft_attn_fwd_nocheck(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
                                            B, H, Lq, Lk, d, int(bool(causal)), scale),
                "fabft_attn_fwd_nocheck")
         return o
-    if out is not None:
-        resid = _check_out(out[1], "out[1] (resid)", (B, H, Lq), torch.float32, dev)
-        flags = _check_out(out[2], "out[2] (flags)", (B, H, Lq), torch.uint8, dev)
-    else:
-        resid = torch.empty((B, H, Lq), dtype=torch.float32, device=dev)
-        flags = torch.empty((B, H, Lq), dtype=torch.uint8, device=dev)
-    _check(_load().fabft_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
+    _check(_LIB.fabft_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
                                resid.data_ptr(), flags.data_ptr(), B, H, Lq, Lk, d,
                                int(bool(causal)), scale), "fabft_attn_fwd")
     return o, resid, flags
@@ -341,25 +354,28 @@ def attn_fwd_twopass(q, k, v, causal: bool = False, scale: float | None = None, 
     the keys, then o, l and c with that fixed max). Returns (o, resid, flags)
     with the meaning of attn_fwd's. out: optional preallocated (o, resid,
     flags)."""
-    import torch
     B, H, Lq, Lk, d = _shape(q, k, v)
     scale = 1.0 / math.sqrt(d) if scale is None else float(scale)
     dev = q.device
     if out is not None:
         if len(out) != 3:
             raise ValueError("out must be (o, resid, flags)")
-        o = _check_out(out[0], "out[0] (o)", q.shape, torch.bfloat16, dev)
-        resid = _check_out(out[1], "out[1] (resid)", (B, H, Lq), torch.float32, dev)
-        flags = _check_out(out[2], "out[2] (flags)", (B, H, Lq), torch.uint8, dev)
+        o = _check_out(out[0], "out[0] (o)", q.shape, _torch.bfloat16, dev)
+        resid = _check_out(out[1], "out[1] (resid)", (B, H, Lq), _torch.float32, dev)
+        flags = _check_out(out[2], "out[2] (flags)", (B, H, Lq), _torch.uint8, dev)
     else:
-        o = torch.empty_like(q)
-        resid = torch.empty((B, H, Lq), dtype=torch.float32, device=dev)
-        flags = torch.empty((B, H, Lq), dtype=torch.uint8, device=dev)
+        o, resid, flags = _outputs(q, B, H, Lq)
     _stream(dev)
-    _check(_load().fabft_attn_fwd_twopass(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
+    _check(_LIB.fabft_attn_fwd_twopass(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
                                        resid.data_ptr(), flags.data_ptr(), B, H, Lq, Lk, d,
                                        int(bool(causal)), scale), "fabft_attn_fwd_twopass")
     return o, resid, flags
+
+
+@functools.lru_cache(maxsize=256)
+def _splitkv_bytes(B: int, H: int, Lq: int, d: int, nsplit: int) -> int:
+    """splitkv_workspace_bytes, remembered per shape (a pure function)."""
+    return splitkv_workspace_bytes(B, H, Lq, d, nsplit)
 
 
 def splitkv_workspace_bytes(B: int, H: int, Lq: int, d: int, nsplit: int) -> int:
@@ -379,6 +395,7 @@ def splitkv_default_splits(B: int, H: int, Lq: int, Lk: int, d: int) -> int:
     return max(1, min(64, -(-512 // (B * H * n_qt)), tiles // 32))
 
 
+@functools.lru_cache(maxsize=256)
 def _launch_splits(B: int, H: int, Lq: int, Lk: int, d: int) -> int:
     """Splits of a call that names none: splitkv_default_splits, and for short
     caches, where that leaves most CUs idle, as many more as give 128
@@ -400,7 +417,6 @@ def attn_fwd_splitkv(q, k, v, causal: bool = False, scale: float | None = None,
     cache. workspace: optional uint8 GPU tensor of at least
     splitkv_workspace_bytes(...) bytes (of splitkv_default_splits(...) without
     nsplit)."""
-    import torch
     B, H, Lq, Lk, d = _shape(q, k, v)
     scale = 1.0 / math.sqrt(d) if scale is None else float(scale)
     dev = q.device
@@ -409,23 +425,21 @@ def attn_fwd_splitkv(q, k, v, causal: bool = False, scale: float | None = None,
         # a workspace sized for the default count stays good for it
         if workspace is not None and \
                 workspace.numel() * workspace.element_size() < \
-                splitkv_workspace_bytes(B, H, Lq, d, nsplit):
+                _splitkv_bytes(B, H, Lq, d, nsplit):
             nsplit = splitkv_default_splits(B, H, Lq, Lk, d)
-    need = splitkv_workspace_bytes(B, H, Lq, d, nsplit)
+    need = _splitkv_bytes(B, H, Lq, d, nsplit)
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
+        workspace = _torch.empty(need, dtype=_torch.uint8, device=dev)
     _check_workspace(workspace, "workspace", need, dev)
     if out is not None:
         o, resid, flags = out
-        _check_out(o, "out[0] (o)", q.shape, torch.bfloat16, dev)
-        _check_out(resid, "out[1] (resid)", (B, H, Lq), torch.float32, dev)
-        _check_out(flags, "out[2] (flags)", (B, H, Lq), torch.uint8, dev)
+        _check_out(o, "out[0] (o)", q.shape, _torch.bfloat16, dev)
+        _check_out(resid, "out[1] (resid)", (B, H, Lq), _torch.float32, dev)
+        _check_out(flags, "out[2] (flags)", (B, H, Lq), _torch.uint8, dev)
     else:
-        o = torch.empty_like(q)
-        resid = torch.empty((B, H, Lq), dtype=torch.float32, device=dev)
-        flags = torch.empty((B, H, Lq), dtype=torch.uint8, device=dev)
+        o, resid, flags = _outputs(q, B, H, Lq)
     _stream(dev)
-    _check(_load().fabft_attn_fwd_splitkv(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
+    _check(_LIB.fabft_attn_fwd_splitkv(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
                                           resid.data_ptr(), flags.data_ptr(), B, H, Lq, Lk, d,
                                           int(bool(causal)), scale, int(nsplit),
                                           workspace.data_ptr(),
@@ -438,7 +452,6 @@ def recompute_flagged(q, k, v, o, resid, flags, causal: bool = False,
                       scale: float | None = None, max_retries: int = 2):
     """Re-run the checked forward on every head with a flagged row (in place,
     up to max_retries times each). Returns (n_recovered, n_persistent)."""
-    import numpy as np
     import torch
     B, H, Lq, Lk, d = _shape(q, k, v)
     scale = 1.0 / math.sqrt(d) if scale is None else float(scale)
@@ -446,13 +459,14 @@ def recompute_flagged(q, k, v, o, resid, flags, causal: bool = False,
     _check_out(resid, "resid", (B, H, Lq), torch.float32, q.device)
     _check_out(flags, "flags", (B, H, Lq), torch.uint8, q.device)
     hf = torch.empty(B * H, dtype=torch.uint8, device=q.device)
-    hf_host = np.zeros(B * H, dtype=np.uint8)
+    # pinned (torch keeps and reuses it): the copy back needs no staging buffer
+    hf_host = torch.empty(B * H, dtype=torch.uint8, pin_memory=True)
     nr, npers = ctypes.c_int(), ctypes.c_int()
     _stream(q.device)
     _check(_load().fabft_recompute_flagged(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
                                            resid.data_ptr(), flags.data_ptr(), B, H, Lq, Lk, d,
                                            int(bool(causal)), scale, hf.data_ptr(),
-                                           hf_host.ctypes.data_as(ctypes.c_void_p),
+                                           hf_host.data_ptr(),
                                            int(max_retries), ctypes.byref(nr),
                                            ctypes.byref(npers)),
            "fabft_recompute_flagged")
