@@ -1908,28 +1908,37 @@ static int launch_t(const FwdParams& p0, hipStream_t stream) {
 // instantiations, below
 template <int D, bool CAUSAL>
 static int launch_c(const FwdParams& p, int mode, hipStream_t s) {
-  if constexpr (D == 96) {
+  if constexpr (D == 96) {   // modes 0 and 1 only
     if (mode == 0) return launch_t<D, CAUSAL, false, false, false, false>(p, s);
-    if (p.kpre) return launch_t<D, CAUSAL, true, false, false, false, true>(p, s);
     return launch_t<D, CAUSAL, true, false, false, false>(p, s);
   } else {
-  if constexpr (D != 256) {   // wide_kernel runs modes 0 and 1 at d = 256
-    if (mode == 0) return launch_t<D, CAUSAL, false, false, false, false>(p, s);
-  }
-  if (mode == 4) return launch_t<D, CAUSAL, true, false, false, false, false, true>(p, s);
-  if (mode == 5) return launch_t<D, CAUSAL, true, true, false, false, false, true>(p, s);
-  if constexpr (D != 256) {
-    // the score check (not built for the one-wave-per-SIMD width 256)
-    if (p.kpre && (mode == 1 || mode == 2)) {
-      if (mode == 1) return launch_t<D, CAUSAL, true, false, false, false, true>(p, s);
-      return launch_t<D, CAUSAL, true, true, false, false, true>(p, s);
+    if constexpr (D != 256) {   // wide_kernel runs modes 0 and 1 at d = 256
+      if (mode == 0) return launch_t<D, CAUSAL, false, false, false, false>(p, s);
+      if (mode == 1) return launch_t<D, CAUSAL, true, false, false, false>(p, s);
     }
-    if (mode == 1) return launch_t<D, CAUSAL, true, false, false, false>(p, s);
-  }
-  if (mode == 3) return launch_t<D, CAUSAL, true, false, false, true>(p, s);
-  return launch_t<D, CAUSAL, true, true, false, false>(p, s);
+    if (mode == 4) return launch_t<D, CAUSAL, true, false, false, false, false, true>(p, s);
+    if (mode == 5) return launch_t<D, CAUSAL, true, true, false, false, false, true>(p, s);
+    if (mode == 3) return launch_t<D, CAUSAL, true, false, false, true>(p, s);
+    return launch_t<D, CAUSAL, true, true, false, false>(p, s);
   }
 }
+
+#if FABFT_PART == 0
+// the score check without the weighted one, modes 1 and 2 (mode 1 at d = 96;
+// not built for the one-wave-per-SIMD width 256). In part 0 at every width:
+// with part 1's scheduler it measured 1-3% slower (causal B=4 H=32 L=4096
+// d=128 655 against 647 us, B=2 H=32 L=2048 d=96 83.2 against 80.8).
+template <int D>
+static int launch_scores(const FwdParams& p, bool causal, int mode, hipStream_t s) {
+  if constexpr (D != 96) {
+    if (mode == 2)
+      return causal ? launch_t<D, true, true, true, false, false, true>(p, s)
+                    : launch_t<D, false, true, true, false, false, true>(p, s);
+  }
+  return causal ? launch_t<D, true, true, false, false, false, true>(p, s)
+                : launch_t<D, false, true, false, false, false, true>(p, s);
+}
+#endif
 
 template <int D, bool CAUSAL>
 static int launch_c_weighted(const FwdParams& p, int mode, hipStream_t s) {
@@ -1993,6 +2002,7 @@ int launch_d256(const FwdParams& p, bool causal, int mode, hipStream_t s) {
 template <int D>
 static int launch_d(const FwdParams& p, bool causal, int mode, hipStream_t s) {
   const bool weighted = p.wcheck && mode != 0;
+  if (!weighted && p.kpre && (mode == 1 || mode == 2)) return launch_scores<D>(p, causal, mode, s);
   if constexpr (D == 128) {
     if (!weighted) return launch_d128_plain(p, causal, mode, s);
   } else {
@@ -2371,9 +2381,11 @@ int launch_fwd(const FwdParams& p, int d, bool causal, int mode, hipStream_t str
   // memory work than on rows zero-padded to 128, bitwise the same result
   // (causal B=2 H=32 L=2048: 73.3 -> 64.2 us with the checksum, 69.8 -> 62.9
   // without). The debug, two-pass and split kernels keep the padded rows.
-  if (d == 96 && mode <= 1)
-    return p.wcheck && mode == 1 ? launch_d_weighted<96>(p, causal, mode, stream)
-                                 : launch_d96_plain(p, causal, mode, stream);
+  if (d == 96 && mode <= 1) {
+    if (p.wcheck && mode == 1) return launch_d_weighted<96>(p, causal, mode, stream);
+    if (p.kpre && mode == 1) return launch_scores<96>(p, causal, mode, stream);
+    return launch_d96_plain(p, causal, mode, stream);
+  }
   if (dc == 128) return launch_d<128>(p, causal, mode, stream);
   return launch_d<64>(p, causal, mode, stream);
 }
