@@ -77,7 +77,9 @@ void set_persistent(int mode);
 int get_persistent();
 int key_tile(int d);
 // Width the kernels compute with for a head dimension d (64, 96, 128 or
-// 256): d itself, or 128 for d = 96 (columns 96..127 are zero on chip).
+// 256): d itself, or 128 for d = 96 (columns 96..127 are zero on chip; the
+// forward of modes 0 and 1 computes 96 columns itself, but the split records and
+// the key prefix sums keep this width).
 inline int compute_width(int d) { return d == 96 ? 128 : d; }
 // Partial-state record of (head, row, split) in the split workspace, in
 // floats: m (exp2 domain), l, c, c_w, then the d unnormalised outputs o.
@@ -93,7 +95,9 @@ int launch_kpre(const uint16_t* k, int BH, int Lk, int d, float* kpre, float* ka
 inline long long kpre_floats(long long BH, int Lk, int d) {
   return BH * ((Lk + 63) / 64 + 1) * (long long)compute_width(d);
 }
-int launch_head_flags(const uint8_t* flags, int BH, int Lq, uint8_t* hflags, hipStream_t stream);
+// hflags_host: null, or pinned host memory (its device address) for a copy
+int launch_head_flags(const uint8_t* flags, int BH, int Lq, uint8_t* hflags, uint8_t* hflags_host,
+                      hipStream_t stream);
 int launch_global(const uint16_t* o, const float* resid, int BH, int Lq, int d, float tau_rel,
                   float tau_abs, double* gsum, uint8_t* gflag, hipStream_t stream);
 

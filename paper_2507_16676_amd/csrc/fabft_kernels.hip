@@ -2582,10 +2582,12 @@ int launch_kpre(const uint16_t* k, int BH, int Lk, int d, float* kpre, float* ka
 
 // ---- per-head OR of the row flags (one workgroup per head). The flags are
 // read 16 at a time from the first 16-byte boundary of the head on (a head of
-// Lq bytes starts anywhere), the bytes before and after one by one.
+// Lq bytes starts anywhere), the bytes before and after one by one. hflags_host
+// (may be null): pinned host memory that takes the same bytes.
 constexpr int kHThreads = 256;
 __global__ __launch_bounds__(kHThreads) void head_flags_kernel(const uint8_t* __restrict__ flags,
-                                                               int Lq, uint8_t* __restrict__ hflags) {
+                                                               int Lq, uint8_t* __restrict__ hflags,
+                                                               uint8_t* __restrict__ hflags_host) {
   __shared__ uint32_t red[kHThreads / 64];
   const int bh = blockIdx.x, tid = threadIdx.x;
   const uint8_t* f = flags + (size_t)bh * Lq;
@@ -2609,12 +2611,15 @@ __global__ __launch_bounds__(kHThreads) void head_flags_kernel(const uint8_t* __
     for (int w = 1; w < kHThreads / 64; ++w) acc |= red[w];
     acc |= acc >> 16;
     hflags[bh] = (uint8_t)(acc | (acc >> 8));
+    if (hflags_host) hflags_host[bh] = (uint8_t)(acc | (acc >> 8));
   }
 }
 
-int launch_head_flags(const uint8_t* flags, int BH, int Lq, uint8_t* hflags, hipStream_t stream) {
+int launch_head_flags(const uint8_t* flags, int BH, int Lq, uint8_t* hflags, uint8_t* hflags_host,
+                      hipStream_t stream) {
   (void)hipGetLastError();
-  hipLaunchKernelGGL(head_flags_kernel, dim3(BH), dim3(kHThreads), 0, stream, flags, Lq, hflags);
+  hipLaunchKernelGGL(head_flags_kernel, dim3(BH), dim3(kHThreads), 0, stream, flags, Lq, hflags,
+                     hflags_host);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -80,3 +80,29 @@ def test_recompute_reports_persistent_heads():
     # O itself is still the fault-free result
     ref = G.oracle_rows(inp, w.causal, w.scale)
     G.compare(o, torch.zeros_like(r), {"O": ref["O"], "pred": np.zeros_like(ref["pred"])}, w.d)
+
+
+@pytest.mark.parametrize("pinned", [True, False])
+@pytest.mark.parametrize("B,H,Lq", [(1, 1, 1), (1, 3, 15), (2, 5, 17), (1, 2, 4099)])
+def test_head_flags_of_every_alignment(B, H, Lq, pinned):
+    """One flagged row at each end and in the middle of a head whose flags start
+    at any byte: exactly those heads are recomputed (and recovered), with the
+    host copy of the head flags in pinned and in pageable memory."""
+    import ctypes
+    print(f"[recompute] head flags B{B} H{H} Lq{Lq} pinned={pinned}", flush=True)
+    w = W.Workload("hf", B, H, Lq, 64, 64, False, 0.125, seed=3)
+    q, k, v = G.dev_inputs(W.make_inputs(w))
+    o, r, f = F.attn_fwd(q, k, v, scale=w.scale)
+    hf = torch.empty(B * H, dtype=torch.uint8, device="cuda")
+    host = torch.full((B * H,), 77, dtype=torch.uint8)
+    host = host.pin_memory() if pinned else host
+    for row in sorted({0, Lq // 2, Lq - 1}):
+        for bh in range(B * H):
+            f.view(B * H, Lq)[bh, row] = 1
+            nr, npers = ctypes.c_int(), ctypes.c_int()
+            rc = F.lib().fabft_recompute_flagged(
+                q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), r.data_ptr(), f.data_ptr(),
+                B, H, Lq, 64, 64, 0, w.scale, hf.data_ptr(), host.data_ptr(), 2,
+                ctypes.byref(nr), ctypes.byref(npers))
+            assert (rc, nr.value, npers.value) == (0, 1, 0), (row, bh)
+            assert int(host.sum()) == 0 and int(hf.sum()) == 0 and int(f.sum()) == 0
