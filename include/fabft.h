@@ -23,7 +23,8 @@
  *    score-check switches and the launch shape as process-global state
  *    (setters are not thread-safe).
  *  - d must be 64, 96, 128 or 256 (d = 96 runs the d = 128 kernels with the
- *    columns 96..127 zero on chip: identical results, 4/3 of the work).
+ *    columns 96..127 zero on chip in the debug, injection, two-pass and split
+ *    paths: identical results, 4/3 of the work).
  *    B, H, Lq, Lk >= 1. scale must be finite and >= 0; a scale below
  *    2^-126 / log2(e) (zero included) runs as that value, which weighs every
  *    visible key alike for scores below 2^100 in magnitude.
@@ -294,8 +295,8 @@ int fabft_get_weighted_check(void);
  * either way (each row is computed by the same instructions in the same
  * order). Modes: FABFT_PERSIST_OFF (one workgroup per item),
  * FABFT_PERSIST_AUTO (default: on for d = 64, 96 and 128 when Lk <= 1024,
- * where a workgroup's start-up is a large part of its work),
- * FABFT_PERSIST_ALWAYS.
+ * where a workgroup's start-up is a large part of its work, unless the launch
+ * runs faster in workgroups of half the rows), FABFT_PERSIST_ALWAYS.
  * fabft_set_persistent returns FABFT_E_MODE for any other value.
  * Process-global, not thread-safe.
  */
