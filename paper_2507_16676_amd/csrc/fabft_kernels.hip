@@ -243,7 +243,8 @@ __device__ __forceinline__ void buffer_load_lds16(i32x4 rsrc, uint32_t voff, uin
 }
 
 // Tile layouts in LDS. A tile row (one key) holds D bf16 = CPR 16-byte
-// chunks; logical chunk c of row r is stored at chunk c ^ swz(r).
+// chunks; logical chunk c of row r is stored at chunk c ^ kswz(r) of K, vst(r, c)
+// of V.
 template <int D>
 struct Tile {
   static constexpr int CPR = D / 8;
@@ -256,19 +257,27 @@ struct Tile {
   static __device__ __forceinline__ int kswz(int r) { return D == 96 ? (r >> 2) & 3 : D >= 128 ? (r & 15) : ((r >> 1) & 7); }
   // V: 32 lanes read 4 consecutive rows x 4 consecutive chunks
   static __device__ __forceinline__ int vswz(int r) { return D == 96 ? 0 : D >= 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1); }
+  // V at d = 256: besides, bits 3 and 4 of a chunk go into its bits 0 and 1,
+  // so that sumrow's reads (4 keys x 4 chunks 8 apart in a pass, else all on
+  // the same quarter of the banks) touch no bank twice; with the padded rows
+  // of the small operand 165.3 -> 163.7 us (causal, B=1 H=16 L=4096). The other
+  // reads take 4 neighbouring chunks and see no difference. Each of vst, the
+  // stored place of logical chunk c of row r, and vlog undoes the other.
+  static __device__ __forceinline__ int vfold(int c) { return D == 256 ? c ^ ((c >> 3) & 3) : c; }
+  static __device__ __forceinline__ int vst(int r, int c) { return vfold(c) ^ vswz(r); }
+  static __device__ __forceinline__ int vlog(int r, int s) { return vfold(s ^ vswz(r)); }
   static __device__ __forceinline__ int kidx(int r, int c) { return r * D + 8 * (c ^ kswz(r)); }
-  static __device__ __forceinline__ int vidx(int r, int c) { return r * D + 8 * (c ^ vswz(r)); }
+  static __device__ __forceinline__ int vidx(int r, int c) { return r * D + 8 * vst(r, c); }
 };
 
 // Rows of the small A operand that yields c and l: sumrow(V) as bf16 hi and
 // lo parts, ones, zeros, and the weighted row sums sum_j (-1)^j V_kj as hi
 // and lo parts, padded to 8 rows. Lane 4b + i of a 4x4x4 product reads row i
 // (VsHi, VsLo, Ones, Zero), for the weighted sums WHi, WLo, Zero, Zero: one
-// wave-wide 16-byte load per 16 keys. Below d = 256 a row holds the tile's 64
+// wave-wide 16-byte load per 16 keys. A row holds the tile's 64
 // keys plus 8 unused ones: with 144-byte rows, rows 0-3 start 36 banks apart
 // and one read touches no bank twice (128-byte rows put rows 0 and 2, and 1
-// and 3, on the same banks). At d = 256 (one wave per SIMD, LDS for two
-// 64 KiB stages) the rows stay 128 bytes.
+// and 3, on the same banks).
 enum { kRowVsHi = 0, kRowVsLo = 1, kRowOnes = 2, kRowZero = 3, kRowWHi = 4, kRowWLo = 5,
        kVsmRows = 8 };
 
@@ -278,7 +287,7 @@ enum { kRowVsHi = 0, kRowVsLo = 1, kRowOnes = 2, kRowZero = 3, kRowWHi = 4, kRow
 // d = 128, the reach of the LDS offset field).
 template <int D, int STAGES = Cfg<D>::STAGES>
 struct Ring {
-  static constexpr int VS = D == 256 ? kBc : kBc + 8;   // vsm row stride (keys)
+  static constexpr int VS = kBc + 8;   // vsm row stride (keys)
   uint16_t k[STAGES][kBc * D];
   uint16_t v[STAGES][kBc * D];
   uint16_t vsm[STAGES][kVsmRows][VS];
@@ -525,7 +534,7 @@ void fwd_kernel(FwdParams p) {
     const int row = slot / CPR, sc = slot % CPR;
     // a chunk past the row's DIO columns reads from offset kv_bytes + soff,
     // past the end of the buffer: zeros
-    const int kc = sc ^ Tile<D>::kswz(row), vc = sc ^ Tile<D>::vswz(row);
+    const int kc = sc ^ Tile<D>::kswz(row), vc = Tile<D>::vlog(row, sc);
     kvo[j] = kc < CIO ? (uint32_t)(row * DIO + 8 * kc) * 2 : kv_bytes;
     vvo[j] = vc < CIO ? (uint32_t)(row * DIO + 8 * vc) * 2 : kv_bytes;
   }
@@ -605,7 +614,7 @@ void fwd_kernel(FwdParams p) {
       // 256-byte rows: no bank conflict. At d = 64: chunk part + 4 j,
       // j = i ^ (key mod 2), so that the keys of one pass take opposite
       // halves of the row, whose banks the V swizzle keeps apart. d = 256
-      // reads CPT consecutive chunks.
+      // reads CPT consecutive chunks (the fold of vst parts the banks).
       const int c = D == 128 || D == 96 ? part + TPK * i
                   : CPT == 2 ? part + TPK * (i ^ (key & 1)) : CPT * part + i;
       const u32x4 ch = *reinterpret_cast<const u32x4*>(&sv[Tile<D>::vidx(key, c)]);
@@ -1383,7 +1392,7 @@ __global__ __launch_bounds__(Cfg<256>::THREADS, 1) void wide_kernel(FwdParams p)
   for (int j = 0; j < NOFF; ++j) {
     const int row = j * kRowStep + tid / CPR, sc = tid % CPR;
     kvo[j] = (uint32_t)(row * D + 8 * (sc ^ Tile<D>::kswz(row))) * 2;
-    vvo[j] = (uint32_t)(row * D + 8 * (sc ^ Tile<D>::vswz(row))) * 2;
+    vvo[j] = (uint32_t)(row * D + 8 * Tile<D>::vlog(row, sc)) * 2;
   }
   const uint32_t ring_lds = (uint32_t)(uintptr_t)(lds_void*)&ring;
   const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(ring_lds + 1024u * wave);
@@ -1432,7 +1441,7 @@ __global__ __launch_bounds__(Cfg<256>::THREADS, 1) void wide_kernel(FwdParams p)
   const int skey = tid / TPK, spart = tid % TPK;
   auto sum_op = [&](int S, SumState& st, int n) __attribute__((always_inline)) {
     if (n < CPT) {
-      // chunks CPT * spart + n; the swizzle of a key is a constant XOR
+      // chunks CPT * spart + n; the swizzle of a key (and part) is a constant XOR
       if (n == 0) {
         st.base = opaque(ring_lds + (uint32_t)offsetof(Ring<D>, v) + S * kStage + 2 * Tile<D>::vidx(skey, CPT * spart));
         st.a = st.aw = 0.f;
@@ -1492,7 +1501,7 @@ __global__ __launch_bounds__(Cfg<256>::THREADS, 1) void wide_kernel(FwdParams p)
     u32x2 part[2];
 #pragma unroll
     for (int t2 = 0; t2 < 2; ++t2) {
-      const uint32_t a = (vt ^ (64u * db)) + (32 * kb + 16 * h + 4 * t2) * kRow;
+      const uint32_t a = (vt ^ (64u * db + 16u * ((db >> 1) & 3))) + (32 * kb + 16 * h + 4 * t2) * kRow;
       part[t2] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)a));
     }
     return u32x4{part[0][0], part[0][1], part[1][0], part[1][1]};
