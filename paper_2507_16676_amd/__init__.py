@@ -423,7 +423,7 @@ def attn_fwd_splitkv(q, k, v, causal: bool = False, scale: float | None = None,
     if nsplit is None:
         nsplit = _launch_splits(B, H, Lq, Lk, d)
         # a workspace sized for the default count stays good for it
-        if workspace is not None and \
+        if isinstance(workspace, _torch.Tensor) and \
                 workspace.numel() * workspace.element_size() < \
                 _splitkv_bytes(B, H, Lq, d, nsplit):
             nsplit = splitkv_default_splits(B, H, Lq, Lk, d)

@@ -111,3 +111,12 @@ def test_rows_past_the_keys_are_never_read(d, Lk, split, causal):
     if pred is not None:
         G.compare(o, pred, ref, d)
     assert int((flags != 0).sum()) == 0
+
+
+def test_splitkv_workspace_not_a_tensor():
+    """A workspace that is no tensor is refused as such, with and without nsplit."""
+    q = torch.zeros(1, 1, 1, 64, dtype=torch.bfloat16, device="cuda")
+    k = torch.zeros(1, 1, 4096, 64, dtype=torch.bfloat16, device="cuda")
+    for nsplit in (None, 2):
+        with pytest.raises(ValueError):
+            F.attn_fwd_splitkv(q, k, k, nsplit=nsplit, workspace=bytearray(1 << 20))
