@@ -477,6 +477,7 @@ def global_check(o, resid):
     """Per-head global check from attn_fwd's o and resid: returns (gsum [B, H]
     fp64 = sum of the row residuals, gflags [B, H] uint8)."""
     import torch
+    _load()   # the checks below need it, and this may be a process's first call
     if o.dtype != torch.bfloat16 or not o.is_cuda or not o.is_contiguous() or o.dim() != 4:
         raise ValueError("o must be a contiguous bf16 [B, H, Lq, d] GPU tensor")
     B, H, Lq, d = o.shape

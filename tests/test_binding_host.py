@@ -1,0 +1,41 @@
+"""Host-side tests of the Python binding: every entry point works as the first
+library call of a process. The tensors are stand-ins that pass for GPU tensors
+up to a check that refuses the call, so nothing is launched."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROLOGUE = """
+import torch
+import paper_2507_16676_amd as F
+
+class T:
+    # a bf16 tensor [1, 1, 8, 64] that says it is on a GPU
+    dtype, is_cuda, shape, device = torch.bfloat16, True, torch.Size((1, 1, 8, 64)), torch.device("cuda", 0)
+    def dim(self): return 4
+    def is_contiguous(self): return True
+
+t, bad = T(), object()
+try:
+    {call}
+except ValueError as e:
+    print("refused:", e)
+"""
+
+
+@pytest.mark.parametrize("call", [
+    "F.global_check(t, bad)",
+    "F.attn_fwd(t, t, t, out=(bad, bad, bad))",
+    "F.attn_fwd_twopass(t, t, t, out=(bad, bad, bad))",
+    "F.attn_fwd_splitkv(t, t, t, workspace=bad)",
+    "F.attn_fwd_inject(t, t, t, out=(bad,) * 5)",
+    "F.recompute_flagged(t, t, t, bad, bad, bad)",
+], ids=lambda c: c[2:c.index("(")])
+def test_first_call_of_a_process(call):
+    r = subprocess.run([sys.executable, "-c", PROLOGUE.format(call=call)], cwd=ROOT, text=True,
+                       capture_output=True, timeout=600)
+    assert r.returncode == 0 and r.stdout.startswith("refused:"), r.stdout + r.stderr
