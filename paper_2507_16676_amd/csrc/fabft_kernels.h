@@ -11,6 +11,25 @@ namespace fabft {
 // waves at d = 256 (one wave per SIMD, for the register file of 512).
 constexpr int query_tile_for(int d) { return d == 256 ? 128 : 256; }
 
+// Tile loads of the d = 256 forward. A workgroup loads 64-row K and V tiles in
+// steps of 16 rows: the step's start goes into the scalar offset of a raw
+// buffer load, the lane's row in the step and its column into the vector offset.
+// The load's range check is vector offset >= size - scalar offset, which refuses
+// a load only while the scalar offset is no larger than the size. Steps past
+// the rows (of the ragged last tile, and of the two tiles past the last one,
+// which every step of the loop issues) therefore start at the size itself,
+// where the check refuses every lane: no memory past the rows is touched, and
+// the rows of tiles that a causal workgroup does not use are not fetched.
+constexpr uint32_t kWideRowBytes = 512, kWideStepBytes = 16 * kWideRowBytes;
+// size: the rows of a head that the key tiles [0, t_end) hold
+constexpr uint32_t wide_load_size(int Lk, int t_end) {
+  return (uint32_t)(Lk < 64 * t_end ? Lk : 64 * t_end) * kWideRowBytes;
+}
+// scalar offset of 16-row step `step` of the head
+constexpr uint32_t wide_load_start(uint32_t step, uint32_t size) {
+  return step * kWideStepBytes < size ? step * kWideStepBytes : size;
+}
+
 // One injected single-bit fault (site numbers and fields as fabft_fault,
 // with the head flattened to bh = b * H + h).
 constexpr int kMaxFaults = 8;

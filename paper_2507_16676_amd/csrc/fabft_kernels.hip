@@ -1340,7 +1340,6 @@ __global__ __launch_bounds__(Cfg<256>::THREADS, 1) void wide_kernel(FwdParams p)
 
   const int Lq = p.Lq, Lk = p.Lk;
   const int off = Lk - Lq;
-  const uint32_t kv_bytes = (uint32_t)Lk * D * 2;
   const float sl2 = p.sl2;
   // key tiles of the workgroup [0, t_end) and of this wave [0, my_end): a wave
   // skips the tiles past its last row's diagonal, and all of them when it
@@ -1386,6 +1385,8 @@ __global__ __launch_bounds__(Cfg<256>::THREADS, 1) void wide_kernel(FwdParams p)
   // apart, two loads span a period of the swizzles (16 rows), so two per-lane
   // offsets per tensor serve them all
   constexpr int kRowStep = kThreads / CPR, NOFF = 16 / kRowStep;
+  constexpr uint32_t kRow = 2 * D;   // bytes per tile row
+  static_assert(kRow == kWideRowBytes, "row size");
   static_assert(kRowStep * CPR == kThreads && NOFF * kRowStep == 16 && NLD % NOFF == 0, "swizzle period");
   uint32_t kvo[NOFF], vvo[NOFF];
 #pragma unroll
@@ -1397,19 +1398,20 @@ __global__ __launch_bounds__(Cfg<256>::THREADS, 1) void wide_kernel(FwdParams p)
   const uint32_t ring_lds = (uint32_t)(uintptr_t)(lds_void*)&ring;
   const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(ring_lds + 1024u * wave);
   const size_t kvbase = (size_t)bh * (size_t)Lk * D;
-  const i32x4 krs = buffer_rsrc(p.k + kvbase, kv_bytes), vrs = buffer_rsrc(p.v + kvbase, kv_bytes);
+  const uint32_t kv_size = __builtin_amdgcn_readfirstlane(wide_load_size(Lk, t_end));
+  const i32x4 krs = buffer_rsrc(p.k + kvbase, kv_size), vrs = buffer_rsrc(p.v + kvbase, kv_size);
   constexpr uint32_t kStage = sizeof(Ring<D>::k[0]), kTile = BC * D * 2;
-  static_assert(kStage == kTile, "a stage holds one tile");
-  // load pair j of a tile of K (V) at byte soff of the head into stage S: two
-  // loads behind one wait for the resource's registers (buffer_load_lds16).
-  // Tiles past the item's last one are loaded too (zeros past the head's end),
-  // so that every step issues the same number of loads; nothing reads them
-  static_assert(NOFF == 2, "the loads of a pair");
-  auto load_op = [&](int S, bool isv, uint32_t soff, int j) __attribute__((always_inline)) {
+  static_assert(kStage == kTile && kTile == 4 * kWideStepBytes, "a stage holds one tile of four steps");
+  // load pair j of tile t of K (V) into stage S: two loads behind one wait for
+  // the resource's registers (buffer_load_lds16). Every step of the loop issues
+  // the same loads, also for tiles past the item's last one: those are refused
+  // as a whole (wide_load_start) and leave zeros that nothing reads
+  static_assert(NOFF == 2 && NOFF * kRowStep * kRow == kWideStepBytes, "the loads of a pair");
+  auto load_op = [&](int S, bool isv, int t, int j) __attribute__((always_inline)) {
     uint32_t m0 = __builtin_amdgcn_readfirstlane(
         wave_lds + (isv ? (uint32_t)offsetof(Ring<D>, v) : (uint32_t)offsetof(Ring<D>, k)) +
         S * kStage + 2 * j * kThreads * 16);
-    const uint32_t so = __builtin_amdgcn_readfirstlane(soff + (uint32_t)(j * 16 * D * 2));
+    const uint32_t so = __builtin_amdgcn_readfirstlane(wide_load_start((uint32_t)(4 * t + j), kv_size));
     asm volatile(
         "s_nop 4\n\tbuffer_load_dwordx4 %1, %3, %4 offen lds\n\t"
         "s_add_u32 m0, m0, %5\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds"
@@ -1421,7 +1423,7 @@ __global__ __launch_bounds__(Cfg<256>::THREADS, 1) void wide_kernel(FwdParams p)
   constexpr int NLP = NLD / 2;
   auto issue = [&](int S, bool isv, int t) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < NLP; ++j) load_op(S, isv, (uint32_t)t * kTile, j);
+    for (int j = 0; j < NLP; ++j) load_op(S, isv, t, j);
   };
 
   // the value, opaque to the optimiser (one instruction per derived address
@@ -1482,7 +1484,6 @@ __global__ __launch_bounds__(Cfg<256>::THREADS, 1) void wide_kernel(FwdParams p)
   // those bits XORed in, plus an immediate offset.
   const int krow = swap_bits23(mrow);
   constexpr int NQK = NDS * NKB, NPV = NKB * 2 * NDB;
-  constexpr uint32_t kRow = 2 * D;   // bytes per tile row
   const uint32_t klane = ring_lds + (uint32_t)offsetof(Ring<D>, k) + 2 * Tile<D>::kidx(krow, grp);
   const int gq = lane >> 4, ll = lane & 15;
   const uint32_t vlane = ring_lds + (uint32_t)offsetof(Ring<D>, v) +
@@ -1629,7 +1630,7 @@ __global__ __launch_bounds__(Cfg<256>::THREADS, 1) void wide_kernel(FwdParams p)
       }
       nx[i / NDS] = mfma32(kop[i], qf[i % NDS], i % NDS == 0 ? f32x16{} : nx[i / NDS]);
 #pragma unroll
-      for (int n = i * NLP / NQK; n < (i + 1) * NLP / NQK; ++n) load_op(SN, true, (uint32_t)(t + 1) * kTile, n);
+      for (int n = i * NLP / NQK; n < (i + 1) * NLP / NQK; ++n) load_op(SN, true, t + 1, n);
 #pragma unroll
       for (int n = i * NSUM / NQK; n < (i + 1) * NSUM / NQK; ++n) sum_op(S, st, n);
 #pragma unroll
@@ -1653,7 +1654,7 @@ __global__ __launch_bounds__(Cfg<256>::THREADS, 1) void wide_kernel(FwdParams p)
       }
       oacc[db] = mfma32(vop[i], pb[kb][h], oacc[db]);
 #pragma unroll
-      for (int n = i * NLP / NPV; n < (i + 1) * NLP / NPV; ++n) load_op(S, false, (uint32_t)(t + 2) * kTile, n);
+      for (int n = i * NLP / NPV; n < (i + 1) * NLP / NPV; ++n) load_op(S, false, t + 2, n);
       if (db == 0) aux_op(S, pb, kb, h, 0);
       if (db == 3) aux_op(S, pb, kb, h, 1);
       if (i < H2) {

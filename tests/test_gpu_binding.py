@@ -113,6 +113,53 @@ def test_rows_past_the_keys_are_never_read(d, Lk, split, causal):
     assert int((flags != 0).sum()) == 0
 
 
+@pytest.mark.parametrize("d", [64, 96, 128, 256])
+@pytest.mark.parametrize("Lk", [66, 77, 161, 1000])   # 2, 13, 33 and 40 rows in the last tile
+@pytest.mark.parametrize("causal", [False, True])
+def test_forward_never_reads_rows_past_the_keys(d, Lk, causal):
+    """The same for the forward itself, which the debug kernel above is not:
+    without a check and with each, in half and in full workgroups (a launch this
+    small takes half ones unless the persistent shape is asked for). Three tiles
+    of NaN rows follow K and V, more than any load reaches."""
+    print(f"[tail] forward Lk={Lk} d={d} causal={causal}", flush=True)
+    w = W.Workload(f"tail{Lk}", 1, 1, 150, Lk, d, causal, d ** -0.5, seed=Lk + d)
+    inp = W.make_inputs(w)
+    q = G.to_dev(inp.q)
+
+    def tailed(bits):
+        n = bits.size
+        buf = torch.full((n + 192 * d,), float("nan"), dtype=torch.bfloat16, device=q.device)
+        buf[:n] = G.to_dev(bits).reshape(-1)
+        return buf[:n].view(1, 1, Lk, d)
+
+    k, v = tailed(inp.k), tailed(inp.v)
+    ref = G.oracle_rows(inp, causal, w.scale)["O"]
+    for mode in (F.PERSIST_AUTO, F.PERSIST_ALWAYS):
+        for check in ("off", "sum", "weighted", "scores"):
+            if check == "scores" and d == 256:
+                continue
+            F.set_persistent(mode)
+            F.set_weighted_check(check == "weighted")
+            if check == "scores":
+                F.set_score_check(torch.empty(F.score_check_workspace_bytes(1, 1, Lk, d),
+                                              dtype=torch.uint8, device=q.device))
+            try:
+                if check == "off":
+                    o = F.attn_fwd(q, k, v, causal=causal, scale=w.scale, check=False)
+                else:
+                    o, resid, flags = F.attn_fwd(q, k, v, causal=causal, scale=w.scale)
+                    assert int((flags != 0).sum()) == 0, (mode, check)
+                    assert bool(torch.isfinite(resid).all()), (mode, check)
+            finally:
+                F.set_persistent(F.PERSIST_AUTO)
+                F.set_weighted_check(False)
+                F.set_score_check(None)
+            O = G.from_dev_bf16(o)
+            assert np.all(np.isfinite(O)), (mode, check)
+            err = np.abs(O - ref)
+            assert err.max() <= G.O_MAX_ABS and err.sum() / np.abs(ref).sum() <= G.O_REL_L1, (mode, check)
+
+
 def test_splitkv_workspace_not_a_tensor():
     """A workspace that is no tensor is refused as such, with and without nsplit."""
     q = torch.zeros(1, 1, 1, 64, dtype=torch.bfloat16, device="cuda")
