@@ -427,6 +427,7 @@ def attn_fwd_splitkv(q, k, v, causal: bool = False, scale: float | None = None,
                 workspace.numel() * workspace.element_size() < \
                 _splitkv_bytes(B, H, Lq, d, nsplit):
             nsplit = splitkv_default_splits(B, H, Lq, Lk, d)
+    nsplit = int(nsplit)   # the sizes below are remembered by value
     need = _splitkv_bytes(B, H, Lq, d, nsplit)
     if workspace is None:
         workspace = _torch.empty(need, dtype=_torch.uint8, device=dev)
@@ -441,7 +442,7 @@ def attn_fwd_splitkv(q, k, v, causal: bool = False, scale: float | None = None,
     _stream(dev)
     _check(_LIB.fabft_attn_fwd_splitkv(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
                                           resid.data_ptr(), flags.data_ptr(), B, H, Lq, Lk, d,
-                                          int(bool(causal)), scale, int(nsplit),
+                                          int(bool(causal)), scale, nsplit,
                                           workspace.data_ptr(),
                                           workspace.numel() * workspace.element_size()),
            "fabft_attn_fwd_splitkv")

@@ -39,3 +39,27 @@ def test_first_call_of_a_process(call):
     r = subprocess.run([sys.executable, "-c", PROLOGUE.format(call=call)], cwd=ROOT, text=True,
                        capture_output=True, timeout=600)
     assert r.returncode == 0 and r.stdout.startswith("refused:"), r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("make", ["np.array(n)", "np.int64(n)", "torch.tensor(n)", "str(n)", "n + 0.5"])
+def test_splitkv_counts_that_are_no_plain_int(make):
+    """nsplit is anything that int() takes, by its value at the call: a count in
+    an array that changes between two calls is sized anew."""
+    code = PROLOGUE.format(call="pass").replace("class T:", "import numpy as np\nclass T:") + f"""
+T.device = torch.device("cpu")
+n = 2
+c = {make}
+for n in (2, 8):
+    if isinstance(c, (np.ndarray, torch.Tensor)):
+        c[...] = n
+    else:
+        c = {make}
+    try:
+        F.attn_fwd_splitkv(t, t, t, nsplit=c, workspace=torch.empty(1, dtype=torch.uint8))
+    except ValueError as e:
+        assert f"{{F.splitkv_workspace_bytes(1, 1, 8, 64, n)}} needed" in str(e), (n, e)
+        print("refused", n)
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, text=True, capture_output=True,
+                       timeout=600)
+    assert r.returncode == 0 and r.stdout.split() == ["refused", "2", "refused", "8"], r.stdout + r.stderr
