@@ -91,6 +91,77 @@ struct FwdParams {
 // on the device at once, each running a list of items, when there are more
 // items than that (set_persistent: off, automatic, always).
 int launch_fwd(const FwdParams& p, int d, bool causal, int mode, hipStream_t stream);
+// Whether workgroups of half the waves (128 query rows) run a forward (modes 0
+// and 1, d = 64, 96 or 128) faster than those of 256 rows on `cus` compute units. A
+// wave alone on its SIMD takes about 0.7 of the time per key tile that two
+// take together, and at d = 64 (96) three (two) half workgroups share a CU,
+// none of them in step with the others, so that one's start-up and epilogue
+// overlap another's products. Measured (us, full -> half workgroups, checksum
+// on; H heads of L):
+//  * every half workgroup has a CU of its own: d = 64, 32 of 512: 14.5 ->
+//    11.0; d = 96, 32 of 256, causal: 10.4 -> 8.2; d = 128: 13.3 -> 10.1.
+//    At d = 128 with at most 128 query rows there is nothing to spread and
+//    the idle waves' share of the loads is missed (4,096 keys: 86 -> 96).
+//  * no more full workgroups than CUs, causal: a light query tile shares the
+//    CU of a heavy one (L = 2048, 32 heads: d = 64 42 -> 35, 96 49 -> 44,
+//    128 59 -> 56; L = 1500: 32 -> 26, 37 -> 31, 44 -> 35), but not with
+//    short rows (L = 1024, 64 heads: 23.8 -> 24.5, 28.0 -> 29.5, level) and not
+//    where all query tiles see about the same keys (few queries over many),
+//    which is as without a mask: two half workgroups do the work of one full one
+//    in the same time. d = 64 gains there in short rows (without a mask 0.90 to
+//    0.985 of the time up to 7 tiles, 1.00 to 1.07 from 8 to 128; with it up to 3:
+//    192 heads of 130 8.2 -> 7.3) and, with the mask, while hardly a CU holds
+//    two (66 heads of 512: 14.1 -> 11.6, 80: 14.5 -> 15.0; 88 heads of 384: 10.7 ->
+//    10.0, 128: 10.9 -> 12.0).
+//  * more than that, at d = 64 where all query tiles see about the same keys
+//    (no mask, or few queries over many keys): rounds decide. Where half
+//    workgroups save a half round of the CUs they win by 10 to 35% (17 heads
+//    of 4,096: 156 -> 117; 300 heads of 256 x 2,048 causal: 82 -> 64), and over
+//    many rounds or in short rows the overlap makes up for taking sumrow and the
+//    loads of K and V twice (192 heads of 1,024 69.7 -> 68.0, 96 of 4,096 480 ->
+//    477, 256 of 512 x 256 0.93). Without a mask long rows of two rounds (beyond 12
+//    tiles) and of three (beyond 32) lose with the checksum or the score check:
+//    by 3 to 5% over 4,096 keys (32 heads: 162 -> 167), 1 to 3% over 2,048 and
+//    0 to 3% over 1,024; three rounds 0 to 2.5% (48 heads of 4,096: 242 -> 245);
+//    without a check (157 -> 153) and with the weighted one (183 -> 181) they
+//    gain or are level, as does one query tile per head (0.975 to 1.0). With the
+//    mask the half order evens the rounds out (0.86 to 1.0) unless two rounds are full,
+//    or nearly: 64 heads of 2,048 x 4,096 128 -> 138 (weighted 145 -> 152), of
+//    2,048 x 8,192 279 -> 284 (weighted 323 -> 312, off 269 -> 262); with short
+//    rows, whose full form is persistent, 256 heads of 512 x 1,024 42.4 -> 44.6
+//    (weighted 47.2 -> 48.8, off 42.0 -> 41.0). (Ranges: several cards.)
+//  * more than that otherwise: with the causal order long rows lose (d = 64,
+//    32 heads of 4,096: 91 -> 109) and short ones gain (L = 700: 33 -> 21). At
+//    d = 96 short rows gain (384 heads of 512: 59.9 -> 58.9, of 128: 23.3 ->
+//    19.3), at d = 128 (one half workgroup per CU: its LDS ring) none do.
+inline bool half_is_faster(int d, bool causal, bool check, bool weighted, int heads, int Lq, int Lk,
+                           int cus) {
+  const int rows = query_tile_for(d);
+  const long long n_qt = ((long long)Lq + rows - 1) / rows;
+  const long long full = heads * n_qt;
+  const long long half = heads * (((long long)Lq + rows / 2 - 1) / (rows / 2));
+  const int tiles = (Lk + 63) / 64;   // of the last query tile
+  // query tiles of about the same work: no mask, or few queries over many keys
+  const bool flat = !causal || 2LL * ((long long)Lk - Lq + rows) >= Lk;
+  if (cus <= 0 || half > 0x7fffffff) return false;
+  if (half <= cus) return d != 128 || half > full;
+  if (full <= cus) {
+    if (!flat) return tiles >= 20;
+    if (d != 64) return false;
+    return causal ? tiles <= 3 || (tiles <= 8 && 8 * half <= 9LL * cus) : tiles <= 7;
+  }
+  if (d == 128) return false;
+  if (d == 64 && flat) {
+    const long long rounds = (full + cus - 1) / cus;
+    if ((half + cus - 1) / cus < 2 * rounds || rounds > 3) return true;
+    const bool plain = check && !weighted;
+    if (!causal) return !plain || n_qt == 1 || tiles <= (rounds == 2 ? 12 : 32);
+    if (rounds == 3 || 16 * full < 30LL * cus) return true;
+    if (n_qt >= 8 && (plain || Lk < 3LL * Lq)) return false;
+    return !check || n_qt == 1 || tiles > 16;
+  }
+  return tiles <= (d == 64 ? 12 : 8);
+}
 enum { kPersistOff = 0, kPersistAuto = 1, kPersistAlways = 2 };
 void set_persistent(int mode);
 int get_persistent();

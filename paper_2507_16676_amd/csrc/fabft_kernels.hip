@@ -1836,44 +1836,6 @@ static int device_cus(hipStream_t stream) {
   return n;
 }
 
-// Whether workgroups of half the waves (128 query rows) run a forward faster
-// than those of p.n_items' 256 rows on `cus` compute units. A wave alone on its
-// SIMD takes about 0.7 of the time per key tile that two take together, and
-// at d = 64 (96) three (two) half workgroups share a CU, none of them in step
-// with the others, so that one's start-up and epilogue overlap another's
-// products. Measured (us, full -> half workgroups, checksum on):
-//  * every half workgroup has a CU of its own: d = 64, 32 heads of 512: 14.5 ->
-//    11.0; d = 96, 32 heads of 256, causal: 10.4 -> 8.2; d = 128: 13.3 -> 10.1.
-//    At d = 128 with at most 128 query rows there is nothing to spread and
-//    the idle waves' share of the loads is missed (4,096 keys: 86 -> 96).
-//  * no more full workgroups than CUs, causal: a light query tile shares the
-//    CU of a heavy one (L = 2048, 32 heads: d = 64 42 -> 35, 96 49 -> 44,
-//    128 59 -> 56; L = 1500: 32 -> 26, 37 -> 31, 44 -> 35), but not with
-//    short rows (L = 1024, 64 heads: 23.8 -> 24.5, 28.0 -> 29.5, level). Without a
-//    mask two half workgroups do the work of one full one in the same time
-//    (d = 64, 64 heads of 1,024: 25.7 -> 26.6; of 512: 17.3 -> 16.8).
-//  * more than that: d = 64 without a mask gains by its three workgroups per
-//    CU at any length (384 heads of 512: 42.6 -> 40.4, of 300: 30.8 -> 23.9;
-//    96 heads of 4,096: 481 -> 468); with the causal order long rows lose (32
-//    heads of 4,096: 91 -> 109) and short ones gain (L = 700: 33 -> 21). At
-//    d = 96 short rows gain (384 heads of 512: 59.9 -> 58.9, of 128: 23.3 ->
-//    19.3), at d = 128 (one half workgroup per CU: its LDS ring) none do.
-template <int D, bool CAUSAL>
-static bool half_is_faster(const FwdParams& p, int cus) {
-  constexpr int kRows = query_tile_for(D) / 2;
-  const long long full = p.n_items;
-  const long long half = full / p.n_qt * ((p.Lq + kRows - 1) / kRows);
-  const int tiles = (p.Lk + kBc - 1) / kBc;   // of the last query tile
-  // query tiles of about the same work: no mask, or few queries over many keys
-  const bool flat = !CAUSAL || 2LL * (p.Lk - p.Lq + 2 * kRows) >= p.Lk;
-  if (cus <= 0) return false;
-  if (half <= cus) return D != 128 || half > full;
-  if (full <= cus) return flat ? D == 64 && tiles <= 8 : tiles >= 20;
-  if (D == 128) return false;
-  if (D == 64 && flat) return half <= INT_MAX;
-  return tiles <= (D == 64 ? 12 : 8) && half <= INT_MAX;
-}
-
 template <int D, bool CAUSAL, bool CHECK, bool INJECT, bool WCHK, bool SPLIT, bool SCHK = false,
           bool TWOPASS = false>
 static int launch_t(const FwdParams& p0, hipStream_t stream) {
@@ -1882,9 +1844,9 @@ static int launch_t(const FwdParams& p0, hipStream_t stream) {
   if constexpr (!INJECT && !SPLIT && !TWOPASS && D != 256) {
     const int cus = device_cus(stream);
     const int mode = g_persist.load();
-    if (mode != kPersistAlways && half_is_faster<D, CAUSAL>(p, cus)) {
+    const int heads = p.n_items / p.n_qt;
+    if (mode != kPersistAlways && half_is_faster(D, CAUSAL, CHECK, WCHK, heads, p.Lq, p.Lk, cus)) {
       constexpr int kRows = query_tile_for(D) / 2;
-      const int heads = p.n_items / p.n_qt;
       p.n_qt = (p.Lq + kRows - 1) / kRows;
       p.grid = p.n_items = heads * p.n_qt;
       (void)hipGetLastError();   // as below
@@ -1898,7 +1860,6 @@ static int launch_t(const FwdParams& p0, hipStream_t stream) {
     // only for short rows (at most 16 key tiles), where a workgroup's
     // start-up is a large part of its work; measured neutral on long rows.
     const int g = cus & ~7;
-    const int heads = p.n_items / p.n_qt;
     const bool want = mode == kPersistAlways ||
                       (mode == kPersistAuto && (p.Lk + kBc - 1) / kBc <= 16);
     if (!SCHK && want && g >= 8 && p.n_items > g && (!CAUSAL || (heads & 7) == 0)) {

@@ -61,3 +61,53 @@ int main() {
 }
 """)
     assert r.returncode == 0, r.stdout
+
+
+# d, causal, check (0 off, 1 sum, 2 weighted), heads, Lq, Lk, half workgroups:
+# both sides of each line of the rule on 256 CUs, with the measured time of
+# half over full workgroups
+HALF = [
+    # as many rounds of the CUs in both forms, two: 1.03, 1.015, 1.04, 1.01; without a
+    # check and weighted 0.98, 0.99; one query tile 0.93; three: 1.015, 0.98
+    (64, 0, 1, 32, 4096, 4096, 0), (64, 0, 1, 64, 2048, 2048, 0), (64, 0, 1, 13, 8192, 8192, 0),
+    (64, 0, 1, 128, 1024, 1024, 0), (64, 0, 0, 32, 4096, 4096, 1), (64, 0, 2, 32, 4096, 4096, 1),
+    (64, 0, 1, 48, 4096, 4096, 0), (64, 0, 1, 64, 4096, 4096, 1),
+    (64, 0, 1, 192, 1024, 1024, 1), (64, 0, 1, 512, 256, 4096, 1),
+    # a half round saved: 0.82, 0.84, 0.77
+    (64, 0, 1, 24, 4096, 4096, 1), (64, 0, 1, 34, 4096, 4096, 1), (64, 1, 1, 300, 256, 2048, 1),
+    # no mask, no more full workgroups than CUs: 0.98 and 1.04, 1.07
+    (64, 0, 1, 192, 256, 448, 1), (64, 0, 1, 96, 512, 512, 0), (64, 0, 1, 32, 2048, 2048, 0),
+    # the same, causal: 0.82, 1.03, 1.03, 1.11, 0.89
+    (64, 1, 1, 66, 512, 512, 1), (64, 1, 1, 80, 512, 512, 0), (64, 1, 1, 128, 512, 512, 0),
+    (64, 1, 1, 128, 350, 350, 0), (64, 1, 1, 192, 130, 130, 1),
+    # causal over more keys than queries, two full rounds: 1.08 (off 1.035, weighted
+    # 1.05), 1.02 (off 0.975, weighted 0.97), 1.05 (off 0.975), 0.95; not full 0.92
+    (64, 1, 1, 64, 2048, 4096, 0), (64, 1, 0, 64, 2048, 4096, 0), (64, 1, 2, 64, 2048, 4096, 0),
+    (64, 1, 1, 64, 2048, 8192, 0), (64, 1, 0, 64, 2048, 8192, 1), (64, 1, 2, 64, 2048, 8192, 1),
+    (64, 1, 1, 256, 512, 1024, 0), (64, 1, 0, 256, 512, 1024, 1), (64, 1, 1, 128, 1024, 2048, 1),
+    (64, 1, 1, 200, 512, 2048, 1),
+    # every half workgroup on its own CU
+    (64, 0, 1, 12, 128, 128, 1), (96, 1, 1, 32, 256, 256, 1), (128, 1, 1, 32, 512, 512, 1),
+    (128, 1, 1, 32, 128, 128, 0),
+    # causal, long rows: 32 heads of 2,048 and 64 of 1,024; of 4,096
+    (128, 1, 1, 32, 2048, 2048, 1), (128, 1, 1, 64, 1024, 1024, 0), (64, 1, 1, 32, 4096, 4096, 0),
+    # short rows of many heads
+    (64, 1, 1, 270, 700, 700, 1), (96, 0, 1, 384, 512, 512, 1), (128, 0, 1, 384, 512, 512, 0),
+]
+
+
+def test_half_workgroup_rule(tmp_path):
+    rows = ",\n".join("{%s}" % ", ".join(map(str, r)) for r in HALF)
+    r = run_cpp(tmp_path, f"""
+int main() {{
+  const int c[][7] = {{{rows}}};
+  for (auto& x : c) printf("%d", (int)half_is_faster(x[0], x[1], x[2] != 0, x[2] == 2, x[3], x[4], x[5], 256));
+  // a device whose CU count is unknown, and more workgroups than a grid holds
+  printf("%d%d", (int)half_is_faster(64, false, true, false, 12, 128, 128, 0),
+         (int)half_is_faster(64, false, true, false, 1 << 30, 300, 300, 256));
+}}
+""")
+    assert r.returncode == 0
+    got = [int(x) for x in r.stdout]
+    assert got[-2:] == [0, 0]
+    assert [(x, g) for x, g in zip(HALF, got) if x[-1] != g] == []
