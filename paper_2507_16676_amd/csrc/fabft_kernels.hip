@@ -1325,7 +1325,12 @@ __global__ __launch_bounds__(Cfg<256>::THREADS, 1) void wide_kernel(FwdParams p)
   constexpr int NLD = BC * CPR / kThreads;   // 16-byte loads per thread per tensor and tile
   static_assert(Cfg<D>::STAGES == 2 && Cfg<D>::WAVES == 4, "one wave per SIMD, two stages");
 
-  __shared__ __attribute__((aligned(16))) Ring<D> ring;
+  // (512: operand addresses take the chunk bits by XOR, which holds only while
+  // every tile row starts on a multiple of its 512 bytes)
+  __shared__ __attribute__((aligned(512))) Ring<D> ring;
+  static_assert(offsetof(Ring<D>, k) % 512 == 0 && offsetof(Ring<D>, v) % 512 == 0 &&
+                sizeof(Ring<D>::k[0]) % 512 == 0 && sizeof(Ring<D>::v[0]) % 512 == 0,
+                "tile rows start on multiples of 512 bytes");
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
