@@ -387,9 +387,10 @@ def splitkv_workspace_bytes(B: int, H: int, Lq: int, d: int, nsplit: int) -> int
 def splitkv_default_splits(B: int, H: int, Lq: int, Lk: int, d: int) -> int:
     """A split count that gives the launch about 512 workgroups (two per CU),
     with at least 32 key tiles per split (shorter splits pay their start-up
-    and merge too often) and at most 64 splits. Measured on decode shapes,
-    one to 64 queries over 8K-128K keys: it picks the fastest count or one
-    within 1% of it."""
+    and merge too often) and at most 64 splits. Measured on decode shapes that
+    fill the device, one to 64 queries over 8K-128K keys: it picks the fastest
+    count or one within 1% of it. Over short caches of few heads attn_fwd_splitkv
+    takes more."""
     n_qt = -(-Lq // query_tile(d))
     tiles = -(-Lk // key_tile(d))
     return max(1, min(64, -(-512 // (B * H * n_qt)), tiles // 32))
@@ -399,14 +400,16 @@ def splitkv_default_splits(B: int, H: int, Lq: int, Lk: int, d: int) -> int:
 def _launch_splits(B: int, H: int, Lq: int, Lk: int, d: int) -> int:
     """Splits of a call that names none: splitkv_default_splits, and for short
     caches, where that leaves most CUs idle, as many more as give 128
-    workgroups (256 with several query rows, whose work per key is larger), of
-    at least 4 key tiles each. Measured (both kernels, us, default -> this): one row,
-    B=1 H=32 Lk=4097 d=128 26.4 -> 18.9, H=8 24.0 -> 15, H=16 d=256 42.2 -> 19.3;
-    16 rows, H=32 Lk=4097 45.8 -> 22.3; 64 rows, H=8 Lk=8192 45.7 -> 20.6."""
+    workgroups (one query row), or as fit on the 256 CUs at once (several rows,
+    whose work per key is larger), of at least 4 key tiles each. Measured (both
+    kernels, us, default -> this): one row, B=1 H=32 Lk=4097 d=128 26.4 -> 18.9,
+    H=8 24.0 -> 15, H=16 d=256 42.2 -> 19.3; 16 rows, H=32 Lk=4097 45.8 -> 22.3; 64
+    rows, H=8 Lk=8192 45.7 -> 20.6. A few workgroups more than CUs cost a second
+    round: B=3 H=5, 4 rows, Lk=29014 d=128, 14 splits 57.5, 18 (270 workgroups) 88.5."""
     ns = splitkv_default_splits(B, H, Lq, Lk, d)
     wgs = B * H * -(-Lq // query_tile(d))
     tiles = -(-Lk // key_tile(d))
-    return max(ns, min(64, -(-(128 if Lq == 1 else 256) // wgs), tiles // 4))
+    return max(ns, min(64, -(-128 // wgs) if Lq == 1 else 256 // wgs, tiles // 4))
 
 
 def attn_fwd_splitkv(q, k, v, causal: bool = False, scale: float | None = None,
@@ -416,7 +419,8 @@ def attn_fwd_splitkv(q, k, v, causal: bool = False, scale: float | None = None,
     defaults to splitkv_default_splits(...), or more of them over a short
     cache. workspace: optional uint8 GPU tensor of at least
     splitkv_workspace_bytes(...) bytes (of splitkv_default_splits(...) without
-    nsplit)."""
+    nsplit; a call takes more splits only if the workspace holds them, which
+    splitkv_workspace_bytes(B, H, Lq, d, 64) always does)."""
     B, H, Lq, Lk, d = _shape(q, k, v)
     scale = 1.0 / math.sqrt(d) if scale is None else float(scale)
     dev = q.device

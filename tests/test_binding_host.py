@@ -63,3 +63,20 @@ for n in (2, 8):
     r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, text=True, capture_output=True,
                        timeout=600)
     assert r.returncode == 0 and r.stdout.split() == ["refused", "2", "refused", "8"], r.stdout + r.stderr
+
+
+def test_launch_splits_stay_within_one_round():
+    """A key-split call that names no count takes more splits than the default
+    only while its workgroups fit on the 256 CUs at once."""
+    import paper_2507_16676_amd as F
+    for B, H, Lq, Lk, d in [(3, 5, 4, 29014, 128), (6, 12, 2, 5177, 128), (3, 16, 40, 8756, 96),
+                            (2, 12, 5, 17439, 256), (11, 5, 312, 648, 256), (12, 16, 16, 686, 256),
+                            (7, 1, 453, 28653, 128), (1, 7, 16, 33901, 64)] + \
+            [(1, H, Lq, 4096, 128) for H in range(1, 300) for Lq in (1, 2, 16, 300)]:
+        default = F.splitkv_default_splits(B, H, Lq, Lk, d)
+        ns = F._launch_splits(B, H, Lq, Lk, d)
+        wgs = B * H * -(-Lq // F.query_tile(d))
+        assert ns == default or (ns > default and ns * wgs <= 256), (B, H, Lq, Lk, d, ns)
+    assert F._launch_splits(1, 32, 1, 4097, 128) == 4      # 128 workgroups
+    assert F._launch_splits(3, 5, 4, 29014, 128) == 17     # 255
+    assert F._launch_splits(1, 32, 16, 4097, 128) == 8     # 256
