@@ -188,6 +188,20 @@ inline long long kpre_floats(long long BH, int Lk, int d) {
 // hflags_host: null, or pinned host memory (its device address) for a copy
 int launch_head_flags(const uint8_t* flags, int BH, int Lq, uint8_t* hflags, uint8_t* hflags_host,
                       hipStream_t stream);
+// Threads per head of the global check. Up to one workgroup per CU there is
+// nothing else to keep loads in flight: 16 waves (B=1 H=32 L=2048 d=128: 256 threads
+// 14, 1,024 9.2 us). With more heads the start of 16 waves per head costs
+// more than the check (4,096 heads of 16 rows, d = 64: 64 threads 3.5, 256 6.2,
+// 1,024 25.1; 2,048 of 256 rows: 256 threads 12.0, 1,024 20.6), except over long
+// heads of many bytes in all (2,048 of 2,048 rows: 96.9, 90.4). A head of at most
+// 512 chunks of 16 bytes takes one wave at any count (8,192 heads of 32 rows: 64
+// threads 5.9, 256 11.0; 32 heads of 64 rows: 3.4 with each). (256: the chip's
+// CUs; asking the runtime costs more than it could gain here.)
+inline int global_threads(int BH, int Lq, int d) {
+  const long long chunks = (long long)Lq * d / 8;
+  if (chunks <= 512) return 64;
+  return BH <= 256 || (chunks >= 8192 && BH * chunks >= (1 << 24)) ? 1024 : 256;
+}
 int launch_global(const uint16_t* o, const float* resid, int BH, int Lq, int d, float tau_rel,
                   float tau_abs, double* gsum, uint8_t* gflag, hipStream_t stream);
 

@@ -2373,12 +2373,10 @@ int key_tile(int d) { return (d == 64 || d == 96 || d == 128 || d == 256) ? kBc 
 // ---- global check of one head (Alg. 3, the check accumulated over all
 // queries; Eq. 5 in its per-query form, Eq. 6-7): R = sum_i (pred_i -
 // actual_i) = sum_i resid_i and A = sum_i sum_j |O_ij|, in fp64, one
-// workgroup per (b, h), with a fixed reduction order (deterministic).
-// With one workgroup per head there are fewer workgroups than CUs, so each is
-// bound by what one CU keeps in flight: 16 waves with kGUnroll loads of 16
-// bytes each, against 4 waves with one load (a latency per 4 KiB) before:
-// B=1 H=32 L=2048 d=128 44.5 -> 10.9 us.
-constexpr int kGThreads = 1024;
+// workgroup per (b, h), with a fixed reduction order (deterministic for a given
+// shape). A CU is bound by the loads it keeps in flight, so a thread has
+// kGUnroll of 16 bytes each and the workgroup's size follows the work
+// (global_threads).
 constexpr int kGUnroll = 4;
 
 __device__ __forceinline__ double wave_sum_f64(double x) {
@@ -2387,6 +2385,7 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
   return x;
 }
 
+template <int kGThreads>
 __global__ __launch_bounds__(kGThreads) void global_check_kernel(
     const uint16_t* __restrict__ o, const float* __restrict__ resid, int Lq, int d,
     float tau_rel, float tau_abs, double* __restrict__ gsum, uint8_t* __restrict__ gflag) {
@@ -2604,8 +2603,15 @@ int launch_head_flags(const uint8_t* flags, int BH, int Lq, uint8_t* hflags, uin
 int launch_global(const uint16_t* o, const float* resid, int BH, int Lq, int d, float tau_rel,
                   float tau_abs, double* gsum, uint8_t* gflag, hipStream_t stream) {
   (void)hipGetLastError();
-  hipLaunchKernelGGL(global_check_kernel, dim3(BH), dim3(kGThreads), 0, stream, o, resid, Lq, d,
-                     tau_rel, tau_abs, gsum, gflag);
+  auto run = [&](auto threads) {
+    hipLaunchKernelGGL(global_check_kernel<decltype(threads)::value>, dim3(BH),
+                       dim3(decltype(threads)::value), 0, stream, o, resid, Lq, d, tau_rel, tau_abs,
+                       gsum, gflag);
+  };
+  const int threads = global_threads(BH, Lq, d);
+  if (threads == 64) run(StageId<64>());
+  else if (threads == 256) run(StageId<256>());
+  else run(StageId<1024>());
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -50,6 +50,36 @@ def test_global_sums_and_eq5(w):
             assert abs(psum[b, h] - ref) <= 5e-3 * max(abs(ref), 1.0) + 2e-2 * np.sqrt(w.Lq), (b, h)
 
 
+@pytest.mark.parametrize("BH,Lq,d", [
+    (1, 1, 64), (3, 5, 96), (5000, 3, 64),          # one wave per head
+    (400, 17, 256), (300, 130, 64), (260, 301, 96),     # four waves
+    (2, 17, 256), (256, 65, 64), (3, 1025, 96), (520, 1100, 256),   # sixteen waves
+])
+def test_global_sums_of_every_workgroup_size(BH, Lq, d):
+    """Sums and flags of random o and resid with one head that is off, one NaN
+    residual and one infinite output, against torch in 64 bits."""
+    print(f"[global] BH{BH} Lq{Lq} d{d}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(BH + Lq)
+    o = torch.randn((1, BH, Lq, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    resid = 1e-6 * torch.randn((1, BH, Lq), generator=g, device="cuda")
+    resid[0, BH // 2, Lq - 1] = 1.0 * d * Lq
+    if BH > 2:
+        resid[0, 0, Lq // 2] = float("nan")
+        o[0, 1, Lq - 1, d - 1] = float("inf")
+    gsum, gflags = F.global_check(o, resid)
+    R = resid.double().sum(-1)
+    A = o.double().abs().sum((-1, -2))
+    # a sum of n terms in 64 bits, in any order
+    bound = 2.0 ** -53 * max(2, Lq) * resid.double().abs().sum(-1)
+    ok = torch.isfinite(R)
+    assert bool(((gsum - R).abs() <= bound)[ok].all()) and bool(torch.isnan(gsum)[~ok].all())
+    tau_rel, tau_abs = F.get_threshold()
+    expect = (R.abs() > tau_rel * A + tau_abs).to(torch.uint8)
+    expect[~ok] = 3
+    assert torch.equal(gflags, expect)
+
+
 def test_global_flag_rule_under_faults():
     w = W.Workload("g_inj", 1, 2, 300, 300, 128, True, 128 ** -0.5, seed=7)
     inp = W.make_inputs(w)

@@ -111,3 +111,20 @@ int main() {{
     got = [int(x) for x in r.stdout]
     assert got[-2:] == [0, 0]
     assert [(x, g) for x, g in zip(HALF, got) if x[-1] != g] == []
+
+
+def test_global_check_threads(tmp_path):
+    """One wave for short heads, sixteen while every head has a CU of its own and
+    for long heads of many bytes, four otherwise."""
+    r = run_cpp(tmp_path, """
+int main() {
+  const int c[][4] = {{12, 64, 64, 64}, {12, 65, 64, 1024}, {5000, 16, 128, 64}, {5000, 1, 256, 64},
+                      {256, 2048, 128, 1024}, {257, 256, 64, 256}, {2048, 1024, 64, 1024},
+                      {2047, 1024, 64, 256}, {5000, 1023, 64, 256}, {1, 1 << 20, 256, 1024},
+                      {300, 65536, 256, 1024}};
+  for (auto& x : c)
+    if (global_threads(x[0], x[1], x[2]) != x[3]) printf("%d %d %d\\n", x[0], x[1], x[2]);
+  return 0;
+}
+""")
+    assert r.returncode == 0 and r.stdout == "", r.stdout
