@@ -243,6 +243,9 @@ float fabft_get_score_threshold(void);
  * not trusted). Counts go to *n_recovered and *n_persistent.
  * head_flags: device buffer of B*H bytes; head_flags_host: host buffer of
  * B*H bytes (both caller-owned scratch; the library allocates nothing).
+ * head_flags_host may be pageable or pinned; pinned memory is written by the
+ * device itself (for up to 2,048 heads, a copy operation less) and must stay
+ * allocated until the call returns.
  * Unlike the other entry points this one synchronises the library stream
  * (it needs the flags on the host). max_retries >= 1.
  */

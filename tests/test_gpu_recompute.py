@@ -82,6 +82,23 @@ def test_recompute_reports_persistent_heads():
     G.compare(o, torch.zeros_like(r), {"O": ref["O"], "pred": np.zeros_like(ref["pred"])}, w.d)
 
 
+@pytest.mark.parametrize("BH", [2048, 2049])
+def test_head_flags_of_many_heads(BH):
+    """Up to 2,048 heads' flags are written to the host by the kernel, more are copied:
+    the flagged heads at both ends and in the middle are the ones recomputed."""
+    print(f"[recompute] {BH} heads", flush=True)
+    w = W.Workload("many", 1, BH, 2, 3, 64, False, 0.125, seed=4)
+    q, k, v = G.dev_inputs(W.make_inputs(w))
+    o, r, f = F.attn_fwd(q, k, v, scale=w.scale)
+    ref = o.clone()
+    for bh in (0, BH // 2, BH - 1):
+        o[0, bh] = 7.0
+        f[0, bh, 1] = 1
+    assert F.recompute_flagged(q, k, v, o, r, f, scale=w.scale) == (3, 0)
+    assert int(f.sum()) == 0 and torch.equal(o.view(torch.int16), ref.view(torch.int16))
+    assert F.recompute_flagged(q, k, v, o, r, f, scale=w.scale) == (0, 0)
+
+
 @pytest.mark.parametrize("pinned", [True, False])
 @pytest.mark.parametrize("B,H,Lq", [(1, 1, 1), (1, 3, 15), (2, 5, 17), (1, 2, 4099)])
 def test_head_flags_of_every_alignment(B, H, Lq, pinned):
