@@ -197,6 +197,31 @@ __device__ __forceinline__ bool nonfinite_bits(float x) {
   return (opaque_bits(x) & 0x7f800000u) == 0x7f800000u;
 }
 
+// The decision on one row, from its residual r = pred - act and absum =
+// sum_j |O_ij|: the threshold is tau_rel * (absum + |pred|) + tau_abs. The
+// non-finite test is on the bits (this file is built with relaxed NaN rules);
+// a non-finite residual also fails the threshold comparison. An overflow of
+// absum (a huge but finite row) would make the threshold infinite and pass
+// any residual, so it counts as non-finite as well.
+struct RowCheck {
+  bool nonfinite;
+  uint32_t f;
+  __device__ __forceinline__ RowCheck(const FwdParams& p, float r, float pred, float absum) {
+    nonfinite = nonfinite_bits(r) || nonfinite_bits(absum);
+    f = (__builtin_fabsf(r) <= p.tau_rel * (absum + __builtin_fabsf(pred)) + p.tau_abs) ? 0 : 1;
+  }
+  // the weighted residual rw = pred_w - sum_j (-1)^j O_ij: the same rule
+  // (|w_j| = 1 keeps absum)
+  __device__ __forceinline__ void weighted(const FwdParams& p, float rw, float pred_w, float absum) {
+    nonfinite = nonfinite || nonfinite_bits(rw);
+    if (!(__builtin_fabsf(rw) <= p.tau_rel * (absum + __builtin_fabsf(pred_w)) + p.tau_abs)) f |= 4;
+  }
+  __device__ __forceinline__ uint8_t flags() {
+    if (nonfinite) f |= 3;
+    return (uint8_t)f;
+  }
+};
+
 // Row r of an MFMA 32-row block reads key 16*(r>>4) + 8*((r>>2)&1) + 4*((r>>3)&1) + (r&3)
 __device__ __forceinline__ int swap_bits23(int r) {
   return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1);
@@ -1206,23 +1231,14 @@ void fwd_kernel(FwdParams p) {
       const float c_tot = sum_xor32(aux[0] + aux[1]);
       const float pred = c_tot * inv;
       const float r = pred - act;
-      const float M = absum + __builtin_fabsf(pred);
-      // non-finite test on the bits (this file is built with relaxed NaN rules);
-      // a non-finite residual also fails the threshold comparison. An overflow
-      // of sum_j |O_ij| (a huge but finite row) would make the threshold
-      // infinite and pass any residual, so it counts as non-finite as well.
-      bool nonfinite = nonfinite_bits(r) || nonfinite_bits(absum);
-      uint8_t f = (__builtin_fabsf(r) <= p.tau_rel * M + p.tau_abs) ? 0 : 1;
-      // weighted check: pred_w = c_w / l against sum_j (-1)^j O_ij (the same
-      // threshold rule; |w_j| = 1 keeps M)
+      RowCheck rc(p, r, pred, absum);
+      // weighted check: pred_w = c_w / l against sum_j (-1)^j O_ij
       float pred_w = 0.f;
       float sc_lhs = 0.f, sc_rhs = 0.f, sc_bound = 0.f;   // score check (debug outputs)
       if constexpr (WCHK) {
         act_w = sum_xor32(act_w);
         pred_w = sum_xor32(auxw[0] + auxw[1]) * inv;
-        const float rw = pred_w - act_w;
-        nonfinite = nonfinite || nonfinite_bits(rw);
-        if (!(__builtin_fabsf(rw) <= p.tau_rel * (absum + __builtin_fabsf(pred_w)) + p.tau_abs)) f |= 4;
+        rc.weighted(p, pred_w - act_w, pred_w, absum);
       }
       if constexpr (SCHK) {
         // score check: sum over the full key tiles of s_ij against
@@ -1260,15 +1276,15 @@ void fwd_kernel(FwdParams p) {
         rhs = sum_xor32(rhs);
         ms = sum_xor32(ms);
         const float rs = lhs - rhs;
-        nonfinite = nonfinite || nonfinite_bits(rs);
-        if (!(__builtin_fabsf(rs) <= p.tau_s * ms + p.tau_abs)) f |= 8;
+        rc.nonfinite = rc.nonfinite || nonfinite_bits(rs);
+        if (!(__builtin_fabsf(rs) <= p.tau_s * ms + p.tau_abs)) rc.f |= 8;
         // masked tiles: the two products' sums must agree bit for bit
-        if (opaque_bits(sum_xor32(d_lhs)) != opaque_bits(sum_xor32(d_rhs))) f |= 8;
+        if (opaque_bits(sum_xor32(d_lhs)) != opaque_bits(sum_xor32(d_rhs))) rc.f |= 8;
         sc_lhs = lhs;
         sc_rhs = rhs;
         sc_bound = ms;
       }
-      if (nonfinite) f |= 3;
+      const uint8_t f = rc.flags();
       if (grp == 0 && qrow < Lq) {
         const size_t ri = (size_t)bh * Lq + qrow;
         p.resid[ri] = r;
@@ -1792,17 +1808,13 @@ __global__ __launch_bounds__(Cfg<256>::THREADS, 1) void wide_kernel(FwdParams p)
     absum = sum_xor32(absum);
     const float pred = sum_xor32(aux[0] + aux[1]) * inv;
     const float r = pred - act;
-    // non-finite residuals and overflowed sums, as in fwd_kernel
-    bool nonfinite = nonfinite_bits(r) || nonfinite_bits(absum);
-    uint8_t f = (__builtin_fabsf(r) <= p.tau_rel * (absum + __builtin_fabsf(pred)) + p.tau_abs) ? 0 : 1;
+    RowCheck rc(p, r, pred, absum);
     if constexpr (WCHK) {
       act_w = sum_xor32(act_w);
       const float pred_w = sum_xor32(auxw[0] + auxw[1]) * inv;
-      const float rw = pred_w - act_w;
-      nonfinite = nonfinite || nonfinite_bits(rw);
-      if (!(__builtin_fabsf(rw) <= p.tau_rel * (absum + __builtin_fabsf(pred_w)) + p.tau_abs)) f |= 4;
+      rc.weighted(p, pred_w - act_w, pred_w, absum);
     }
-    if (nonfinite) f |= 3;
+    const uint8_t f = rc.flags();
     if (grp == 0 && qrow < Lq) {
       const size_t ri = (size_t)bh * Lq + qrow;
       p.resid[ri] = r;
@@ -2070,17 +2082,13 @@ __global__ __launch_bounds__(64 * kMergeWaves) void merge_kernel(FwdParams p, in
   absum = wave_sum(absum);
   const float pred = c * inv;
   const float r = pred - act;
-  // as in the forward epilogue: an overflowed sum_j |O_ij| counts as non-finite
-  bool nonfinite = nonfinite_bits(r) || nonfinite_bits(absum);
-  uint8_t f = (__builtin_fabsf(r) <= p.tau_rel * (absum + __builtin_fabsf(pred)) + p.tau_abs) ? 0 : 1;
+  RowCheck rc(p, r, pred, absum);
   if constexpr (WCHK) {
     act_w = wave_sum(act_w);
     const float pred_w = cw * inv;
-    const float rw = pred_w - act_w;
-    nonfinite = nonfinite || nonfinite_bits(rw);
-    if (!(__builtin_fabsf(rw) <= p.tau_rel * (absum + __builtin_fabsf(pred_w)) + p.tau_abs)) f |= 4;
+    rc.weighted(p, pred_w - act_w, pred_w, absum);
   }
-  if (nonfinite) f |= 3;
+  const uint8_t f = rc.flags();
   if (lane == 0) {
     const size_t ri = (size_t)bh * rows_per_head + row;
     p.resid[ri] = r;
