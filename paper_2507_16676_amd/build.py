@@ -56,8 +56,9 @@ KERNEL_FLAGS = ["-mno-amdgpu-ieee", "-fno-honor-nans",
 
 
 # The kernel source is compiled three times (FABFT_PART 0 to 2, see its head):
-# part 1, the d = 128 forward kernels without the weighted check, with LLVM's
-# iterative ILP scheduler; part 2, the d = 256 forward kernels.
+# part 1, the d = 128 kernels and the d = 96 forward without the weighted and the
+# score check, with LLVM's iterative ILP scheduler; part 2, the d = 256 kernels,
+# with the flags of part 0 and beside it in time.
 PART1_FLAGS = ["-DFABFT_PART=1", "-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]
 PART2_FLAGS = ["-DFABFT_PART=2"]
 

@@ -78,15 +78,19 @@
 
 #include "fabft_kernels.h"
 
-// This file is compiled three times. Part 1 holds the d = 128 forward kernels
-// without the weighted check and is built with LLVM's iterative ILP scheduler,
-// measured 2-3% faster for them (and 2-4% slower at d = 64). Part 2 holds the
-// d = 256 forward kernels and is built with the MFMA results in vector
-// registers first (-amdgpu-mfma-vgpr-form): by default LLVM puts every MFMA
-// result into the accumulation registers of these 512-register kernels and
-// copies the scores out and the outputs back and forth, about 400 copies per
-// key tile and wave, against about 50. Part 0 holds everything else. A kernel
-// is instantiated in one part only.
+// This file is compiled three times. Part 1 holds the d = 128 kernels and the
+// d = 96 forward without the weighted and the score check and is built with
+// LLVM's iterative ILP scheduler, measured 2-3% faster for them (and 2-4% slower
+// at d = 64, 1-3% slower with the score check). Part 2 holds the d = 256
+// kernels but decode; it is a part of its own only so that the build compiles it
+// beside part 0, which holds everything else. A kernel is instantiated in one
+// part only.
+// All parts are built with the MFMA results in vector registers first
+// (-amdgpu-mfma-vgpr-form): by default LLVM puts every MFMA result into the
+// accumulation registers of the 512-register kernels at d = 256 and copies the
+// scores out and the outputs back and forth, about 400 copies per key tile and
+// wave, against about 50. The code of the kernels with 256 registers at most is the
+// same with and without it.
 #ifndef FABFT_PART
 #define FABFT_PART 0
 #endif
@@ -1617,7 +1621,7 @@ __global__ __launch_bounds__(Cfg<256>::THREADS, 1) void wide_kernel(FwdParams p)
 
   // A branch that is never taken, to end the basic block: with the loop's
   // head, the row sums and the products in one block the register allocator
-  // spills (no instantiation does with the split).
+  // spills to scratch (with the split no instantiation uses scratch).
   auto split_block = [&]() __attribute__((always_inline)) {
     if (Lq < 0) asm volatile("s_nop 0");
   };
