@@ -9,8 +9,8 @@
 // actual = sum_j O_ij.
 //
 // Dataflow. One workgroup = 8 waves = 256 query rows (one workgroup per CU,
-// two waves per SIMD; at d = 256, 4 waves and one; half of that for small
-// launches and short rows, half_is_faster); one wave = 32 rows; key tiles of
+// two waves per SIMD; at d = 256, 4 waves and one; below d = 256 half of that
+// where it is faster, half_is_faster); one wave = 32 rows; key tiles of
 // 64 keys. The d = 256 forward (wide_kernel) overlaps a tile's softmax with
 // the next tile's scores, everything else below is the same.
 //  * The 32x32x16 bf16 MFMA computes S^T = K Q^T (keys on the M side, the
@@ -115,8 +115,8 @@ typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 // and a 2-stage ring (64 KiB per stage). D = 64 runs 8 waves like D = 128
 // with a 4-stage ring of 69 KiB; sumrow there is taken once per key tile for
 // 256 query rows rather than twice for two 4-wave workgroups of 128 rows
-// each (7-8% faster with the checksum on 2,048- and 4,096-key rows; shorter
-// rows run in half workgroups with their own ring, half_is_faster).
+// each (7-8% faster with the checksum on 2,048- and 4,096-key rows; launches
+// that run faster in half workgroups, half_is_faster, have a ring of their own).
 template <int D>
 struct Cfg {
   static constexpr int WAVES = (D == 256) ? 4 : 8;
