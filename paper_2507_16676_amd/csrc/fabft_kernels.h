@@ -133,7 +133,11 @@ int launch_fwd(const FwdParams& p, int d, bool causal, int mode, hipStream_t str
 //  * more than that otherwise: with the causal order long rows lose (d = 64,
 //    32 heads of 4,096: 91 -> 109) and short ones gain (L = 700: 33 -> 21). At
 //    d = 96 short rows gain (384 heads of 512: 59.9 -> 58.9, of 128: 23.3 ->
-//    19.3), at d = 128 (one half workgroup per CU: its LDS ring) none do.
+//    19.3); so do longer ones where half a round is saved (24 heads of 4,096
+//    without a mask 190 -> 173), which this rule does not use. At d = 128 (one half
+//    workgroup per CU: its LDS ring) whole query tiles lose (384 heads of 512
+//    53 -> 70); mostly empty last tiles gain (414 heads of 330 x 272 without a
+//    check 61 -> 55), not used either.
 inline bool half_is_faster(int d, bool causal, bool check, bool weighted, int heads, int Lq, int Lk,
                            int cus) {
   const int rows = query_tile_for(d);
